@@ -141,7 +141,7 @@ F32::elem* links_of<F32>(mspcg_ctx* c) { return c->L32; }
 template <>
 F16::elem* links_of<F16>(mspcg_ctx* c) { return c->L16; }
 
-long hop_nparts(mspcg_ctx* c) { return hop_grid_x<F64>(c->Vh, c->Ls); }
+long hop_nparts(mspcg_ctx* c) { return hop_grid_x(c->Vh, c->Ls, 1, true); }
 
 void pick_tile(const int pref[4], const Box& b, int out[4]) {
     bool any = false;
@@ -206,7 +206,7 @@ static int op_hop_ex(mspcg_ctx* c, Field<S> out, CField<S> in, int out_par, bool
     }
     const double bytes = (double)c->Nh * S::bytes_spinor * passes + (double)c->Vh * 8 * S::bytes_link;
     Timed t(c, cg ? MSPCG_KC_HOPCG : kc_hop<S>(), bytes, st);
-    return launch_hop<S>(a, c->Ls, 1, dag, st);
+    return launch_hop<S>(a, c->Ls, 1, dag, true, st);
 }
 
 template <class S>

@@ -4,8 +4,9 @@
 
 namespace mspcg {
 
-template int launch_hop<F64>(const HopArgs<F64>&, int, int, bool, hipStream_t);
-template long hop_grid_x<F64>(long, int);
+MSPCG_HOP_WIDE(MSPCG_HOP_EXTERN, F64)
+
+template int launch_hop<F64>(const HopArgs<F64>&, int, int, bool, bool, hipStream_t);
 template int launch_multi_hop<F64>(const MultiHop<F64>*, long, int, bool, bool, bool,
                                     bool, hipStream_t);
 

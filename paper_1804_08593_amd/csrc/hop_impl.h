@@ -861,7 +861,7 @@ __global__ __launch_bounds__(256, (hop_min_waves<S, LS, EPA, CG>())) void hop_ke
 }
 
 template <class S, int LS>
-static void launch_ls(const HopArgs<S>& a, int ndom, bool dag, hipStream_t st) {
+void launch_ls(const HopArgs<S>& a, int ndom, bool dag, hipStream_t st) {
     constexpr int SPB = 256 / LS;
     const long nout = a.site_list ? a.n_list : a.g.out.Vh;
     dim3 grid((unsigned)((nout + SPB - 1) / SPB), (unsigned)ndom);
@@ -897,12 +897,25 @@ static void launch_ls(const HopArgs<S>& a, int ndom, bool dag, hipStream_t st) {
 #undef MSPCG_HOP_LAUNCH
 }
 
+// Each precision's kernels compile as two translation units: hop_<S>.hip holds
+// launch_hop, the multi-lattice kernels and the smaller Ls, hop_<S>_wide.hip
+// the Ls below.
+#define MSPCG_HOP_WIDE(X, S) X(S, 12) X(S, 16) X(S, 20) X(S, 24) X(S, 32)
+#define MSPCG_HOP_INST(S, L) \
+    template void launch_ls<S, L>(const HopArgs<S>&, int, bool, hipStream_t);
+#define MSPCG_HOP_EXTERN(S, L) \
+    extern template void launch_ls<S, L>(const HopArgs<S>&, int, bool, hipStream_t);
+
 template <class S>
-int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, hipStream_t st) {
+int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipStream_t st) {
     if (a.cg_r.data && (!dag || !a.partials)) return -1;
     // FP16-storage hops address a domain's input sites with 32-bit offsets
     const long site_bytes = (long)Ls * Chunk<S>::K * 16;
     if (S::has_scale && (a.g.in.Vh >= (1L << 24) || a.g.in.Vh * site_bytes > 0xffffffffL)) return -1;
+    if (small && hop_is_small(a.site_list ? a.n_list : a.g.out.Vh, Ls, ndom)) {
+        if (launch_hop_small<S>(a, Ls, ndom, dag, st)) return -1;
+        return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
     switch (Ls) {
 #define MSPCG_CASE(L) \
     case L: launch_ls<S, L>(a, ndom, dag, st); break;
@@ -911,12 +924,6 @@ int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, hipStream_t st) 
         default: return -1;
     }
     return hipGetLastError() == hipSuccess ? 0 : -2;
-}
-
-template <class S>
-long hop_grid_x(long Vh, int Ls) {
-    const int spb = 256 / Ls;
-    return (Vh + spb - 1) / spb;
 }
 
 // One launch over a work list of several lattices that share Ls (launch

@@ -55,8 +55,11 @@ struct HopArgs {
     long n_list;
 };
 
+// small: the small-launch kernel (hop_small.h) may be used
 template <class S>
-int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, hipStream_t st);
+int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipStream_t st);
+template <class S>
+int launch_hop_small(const HopArgs<S>& a, int Ls, int ndom, bool dag, hipStream_t st);
 
 // Several lattices' block-domain hops of one stage in one persistent launch.
 // The work list is (lattice i, domain d, workgroup bx): lattice i owns items
@@ -79,8 +82,17 @@ bool multi_hop_ls(int Ls);  // Ls handled by the multi-lattice kernel
 template <class S>
 int launch_multi_hop(const MultiHop<S>* dev, long items, int Ls, bool dag, bool eph, bool epa,
                      bool cg, hipStream_t st);
-template <class S>
-long hop_grid_x(long Vh, int Ls);  // workgroups per domain for Vh output sites
+// workgroups per domain for Vh output sites on each of ndom domains; small: the
+// small-launch kernel may be used
+long hop_grid_x(long Vh, int Ls, int ndom, bool small);
+// Whether a launch onto Vh sites of each of ndom domains takes the small-launch
+// kernel.  hop_body's time hardly depends on the size while every CU holds at most
+// one of its workgroups (65536 entries); the small kernel's grows with the size
+// from a lower start.  Microseconds per FP64 CG iteration (4 hops; hop_body /
+// small): 4^4x8 71 / 56, 8^4x8 (16384 entries) 97 / 61, 8^4x12 92 / 69, 8^4x16 90 /
+// 75, 8^3x16x8 (32768) 99 / 73, 8^4x24 (49152) 97 / 138, 8^3x16x16 (65536) 102 /
+// 112, 12^4x8 (82944) 137 / 142, 12^4x12 156 / 188.
+inline bool hop_is_small(long Vh, int Ls, int ndom) { return Vh * Ls * ndom <= 42000; }
 
 // out = P(in) on one box per domain (optionally |out|^2 partials).
 template <class S>

@@ -382,7 +382,7 @@ static int dom_hop(mspcg_ctx* c, Field<S> out, const Box& bout, CField<S> in, co
     const HopArgs<S> a = dom_hop_args<S>(c, out, bout, in, bin, out_par, ph, aux, baux, pa,
                                          partials, done, cg, list, nlist, nread, bytes);
     Timed t(c, cg ? MSPCG_KC_HOPDOMCG : MSPCG_KC_HOPDOM, bytes, st);
-    return launch_hop<S>(a, c->Ls, c->dom.ndom, dag, st);
+    return launch_hop<S>(a, c->Ls, c->dom.ndom, dag, true, st);
 }
 
 template <class S>
@@ -417,7 +417,7 @@ static int dom_fived(mspcg_ctx* c, Field<S> out, CField<S> in, long Vh, const Fi
 
 // w = A_s p for every block: P_s Mhat_D^+ Mhat_D p (p supported on the block).
 // partials (optional) receive per-domain |Mhat_D p|^2 = <p, A_s p>, laid out
-// [ndom][hop_grid_x(n_y)] (pad2.Vh in place of n_y when pad = 0).
+// [ndom][hop_grid_x of the y hop].
 template <class S>
 int block_A(mspcg_ctx* c, Field<S> w, CField<S> p, double* partials, const int* done,
             hipStream_t st) {
@@ -485,6 +485,7 @@ struct Local {
     Field<S> rho, p, zz, t, u, y, v;
     InnerScalars sc;
     long hop_np = 0, start_np = 0, upd_np = 0;
+    bool small = true;  // the small-launch hop may be used
     FiveDProg m14;
 };
 
@@ -507,13 +508,14 @@ static int local_init(mspcg_ctx* c, Local<S>& L) {
         return MSPCG_ENOMEM;
     L.sc = inner_scalars(c);
     if (!L.sc.gam || !L.sc.a || !L.sc.beta || !L.sc.active) return MSPCG_ENOMEM;
-    L.hop_np = hop_grid_x<S>(D.yout(), Ls);
+    L.hop_np = hop_grid_x(D.yout(), Ls, D.ndom, L.small);
     const int spb = kThreads / Ls;
     L.start_np = (D.interior.Vh + spb - 1) / spb;
     // partials of the fused update: one per workgroup of the interior hop
-    L.upd_np = hop_grid_x<S>(D.interior.Vh, Ls);
+    L.upd_np = hop_grid_x(D.interior.Vh, Ls, D.ndom, L.small);
     const long vec_np = (nd + kThreads - 1) / kThreads;
     long need = L.hop_np > L.start_np ? L.hop_np : L.start_np;
+    if (L.upd_np > need) need = L.upd_np;
     if (vec_np > need) need = vec_np;
     int e = ensure_partials(c, (size_t)(D.ndom * need + 64));
     if (e) return e;
@@ -643,7 +645,7 @@ static int precond_core(mspcg_ctx* c, int l, CField<F64> r, Field<F64> z, const 
             const HopArgs<S> a = local_hop<S>(L, k, it, l, done, bytes, dag);
             {
                 Timed t(c, k == 3 ? MSPCG_KC_HOPDOMCG : MSPCG_KC_HOPDOM, bytes, st);
-                if (launch_hop<S>(a, c->Ls, c->dom.ndom, dag, st)) return MSPCG_EHIP;
+                if (launch_hop<S>(a, c->Ls, c->dom.ndom, dag, L.small, st)) return MSPCG_EHIP;
             }
             if (k == 1 && (e = local_alpha<S>(L, done, st))) return e;
         }
@@ -711,7 +713,7 @@ struct BatchPrecondImpl : BatchPrecond {
                 }
                 h[k].a[j] = a;
                 h[k].ls[j] = G.Ls;
-                h[k].gx[j] = (int)hop_grid_x<S>(nout, G.Ls);
+                h[k].gx[j] = (int)hop_grid_x(nout, G.Ls, 1, false);
                 h[k].first[j] = first;
                 first += (long)L[i].c->dom.ndom * h[k].gx[j];
             }
@@ -759,7 +761,8 @@ struct BatchPrecondImpl : BatchPrecond {
             double bytes;
             bool dg;
             const HopArgs<S> a = local_hop<S>(L[i], k, it, l, done[i], bytes, dg);
-            if (launch_hop<S>(a, L[i].c->Ls, L[i].c->dom.ndom, dg, st)) return MSPCG_EHIP;
+            if (launch_hop<S>(a, L[i].c->Ls, L[i].c->dom.ndom, dg, L[i].small, st))
+                return MSPCG_EHIP;
         }
         return 0;
     }
@@ -795,8 +798,14 @@ static int make_batch_impl(mspcg_ctx* const* cs, int n, int l, const int* const*
     b->L.resize(n);
     b->done.assign(done, done + n);
     int e;
-    for (int i = 0; i < n; ++i)
+    // where the persistent launches are possible, their workgroups set the order
+    // of the sums and both forms of the batch use them
+    bool all = true;
+    for (int i = 0; i < n; ++i) all = all && multi_hop_ls(cs[i]->Ls);
+    for (int i = 0; i < n; ++i) {
+        b->L[i].small = !all;
         if ((e = local_init<S>(cs[i], b->L[i]))) return e;
+    }
     if (multi && l > 0) {
         e = b->build(l);
         if (e && e != MSPCG_EUNSUPPORTED) return e;
@@ -820,7 +829,13 @@ size_t precond_partials_need(mspcg_ctx* c) {
     const Domains& D = c->dom;
     const int Ls = c->Ls;
     const long nd = D.interior.Vh * Ls;
-    const long hop_np = hop_grid_x<F64>(D.yout(), Ls);
+    long hop_np = 0;  // with the small-launch hop and without
+    for (const bool sm : {false, true}) {
+        const long n = hop_grid_x(D.yout(), Ls, D.ndom, sm);
+        if (n > hop_np) hop_np = n;
+    }
+    const long u = hop_grid_x(D.interior.Vh, Ls, D.ndom, true);
+    if (u > hop_np) hop_np = u;
     const int spb = kThreads / Ls;
     const long start_np = (D.interior.Vh + spb - 1) / spb;
     const long vec_np = (nd + kThreads - 1) / kThreads;
