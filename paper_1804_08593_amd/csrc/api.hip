@@ -171,10 +171,18 @@ static int kc_hop() {
                                                                       : MSPCG_KC_HOPDOM);
 }
 
+// full: write a boundary field instead of `out` (zeros on the other parity's
+// sites when zero_other)
+struct ToFull {
+    double2* full;
+    int zero_other;
+};
+
 template <class S>
 static int op_hop_ex(mspcg_ctx* c, Field<S> out, CField<S> in, int out_par, bool dag,
                      const FiveDProg& ph, const CField<S>* aux, const FiveDProg& pa,
-                     double* partials, const int* done, const CgUpdate<S>* cg, hipStream_t st) {
+                     double* partials, const int* done, const CgUpdate<S>* cg, hipStream_t st,
+                     const ToFull* full = nullptr) {
     HopArgs<S> a;
     memset(&a, 0, sizeof(a));
     a.in = in;
@@ -193,6 +201,11 @@ static int op_hop_ex(mspcg_ctx* c, Field<S> out, CField<S> in, int out_par, bool
     a.done = done;
     a.xcd_remap = c->tune.xcd_remap;
     pick_tile(c->tune.tile[prec_index<S>()], c->lat, a.tile);
+    if (full) {
+        a.bout = full->full;
+        a.V4 = c->V4;
+        a.zero_other = full->zero_other;
+    }
     // spinor passes: in, out, aux; a fused CG update reads r, x, p and writes
     // r, x (and out only if it is kept)
     int passes = 2 + (aux ? 1 : 0);
@@ -232,28 +245,45 @@ int op_fived(mspcg_ctx* c, Field<S> out, CField<S> in, const FiveDProg& p, doubl
     return launch_fived<S>(a, c->Ls, 1, st);
 }
 
+// y = Mhat p (even) with t = B p given
+template <class S>
+static int mhat_hops(mspcg_ctx* c, Field<S> y, CField<S> p, CField<S> t, double* partials,
+                     const int* done, hipStream_t st, const ToFull* full = nullptr) {
+    const std::string pfx = std::is_same<S, F64>::value ? "d." : "s.";
+    Field<S> u = half_field<S>(c, pfx + "mh_u", c->Nh);
+    if (!u.data) return MSPCG_ENOMEM;
+    int e;
+    if ((e = op_hop<S>(c, u, t, 1, false, c->pr.X, nullptr, c->pr.id, nullptr, done, st))) return e;
+    return op_hop_ex<S>(c, y, cfield(u), 0, false, prog_scale(-0.25), &p, c->pr.M5, partials, done,
+                        nullptr, st, full);
+}
+
 template <class S>
 int op_mhat(mspcg_ctx* c, Field<S> y, CField<S> p, double* partials, const int* done,
             hipStream_t st) {
     const std::string pfx = std::is_same<S, F64>::value ? "d." : "s.";
     Field<S> t = half_field<S>(c, pfx + "mh_t", c->Nh);
-    Field<S> u = half_field<S>(c, pfx + "mh_u", c->Nh);
     int e;
     if ((e = op_fived<S>(c, t, p, c->pr.B, nullptr, done, st))) return e;
-    if ((e = op_hop<S>(c, u, cfield(t), 1, false, c->pr.X, nullptr, c->pr.id, nullptr, done, st)))
+    return mhat_hops<S>(c, y, p, cfield(t), partials, done, st);
+}
+
+template <class S>
+static int mhatdag_hops(mspcg_ctx* c, Field<S> q, CField<S> y, const int* done, hipStream_t st,
+                        const ToFull* full) {
+    const std::string pfx = std::is_same<S, F64>::value ? "d." : "s.";
+    Field<S> v = half_field<S>(c, pfx + "mh_v", c->Nh);
+    if (!v.data) return MSPCG_ENOMEM;
+    int e;
+    if ((e = op_hop<S>(c, v, y, 1, true, c->pr.Xdag, nullptr, c->pr.id, nullptr, done, st)))
         return e;
-    return op_hop<S>(c, y, cfield(u), 0, false, prog_scale(-0.25), &p, c->pr.M5, partials, done, st);
+    return op_hop_ex<S>(c, q, cfield(v), 0, true, scaled(c->pr.Bdag, -0.25, -0.25), &y,
+                        c->pr.M5dag, nullptr, done, nullptr, st, full);
 }
 
 template <class S>
 int op_mhatdag(mspcg_ctx* c, Field<S> q, CField<S> y, const int* done, hipStream_t st) {
-    const std::string pfx = std::is_same<S, F64>::value ? "d." : "s.";
-    Field<S> v = half_field<S>(c, pfx + "mh_v", c->Nh);
-    int e;
-    if ((e = op_hop<S>(c, v, y, 1, true, c->pr.Xdag, nullptr, c->pr.id, nullptr, done, st)))
-        return e;
-    return op_hop<S>(c, q, cfield(v), 0, true, scaled(c->pr.Bdag, -0.25, -0.25), &y, c->pr.M5dag,
-                     nullptr, done, st);
+    return mhatdag_hops<S>(c, q, y, done, st, nullptr);
 }
 
 // One CG step around q = A p with the vector updates fused into the operator
@@ -525,80 +555,89 @@ extern "C" int mspcg_get_warnings(mspcg_ctx* c, int* warnings) try {
 }
 MSPCG_ABI_CATCH
 
+// mspcg_apply's operators between boundary fields: the input is packed with its
+// first 5D factor formed in the same pass, and the last hop writes the boundary
+// field itself.
 template <class S>
 static int apply_prec(mspcg_ctx* c, int op, const double2* in, double2* out, hipStream_t st) {
     const std::string pfx = std::is_same<S, F64>::value ? "d." : "s.";
-    Field<S> ie = half_field<S>(c, pfx + "ap_ie", c->Nh);
-    Field<S> io = half_field<S>(c, pfx + "ap_io", c->Nh);
-    Field<S> oe = half_field<S>(c, pfx + "ap_oe", c->Nh);
-    Field<S> oo = half_field<S>(c, pfx + "ap_oo", c->Nh);
-    if (!ie.data || !io.data || !oe.data || !oo.data) return MSPCG_ENOMEM;
-    const bool full = op == MSPCG_OP_D || op == MSPCG_OP_DDAG || op == MSPCG_OP_HOP ||
-                      op == MSPCG_OP_HOPDAG || op == MSPCG_OP_M5INV || op == MSPCG_OP_PREPARE;
+    const Progs& P = c->pr;
     int e = 0;
 #define T_(x)                           \
     do {                                \
         if ((e = (x)) != 0) return e < 0 ? MSPCG_EHIP : e; \
     } while (0)
-    T_(launch_pack_parity<S>(in, ie, c->L, c->Ls, 0, st));
-    if (full) T_(launch_pack_parity<S>(in, io, c->L, c->Ls, 1, st));
-    const Progs& P = c->pr;
+    if (op == MSPCG_OP_M5INV) {
+        T_(launch_prog_full<S>(in, out, P.M5inv, c->act.mf, c->L, c->Ls, st));
+        return MSPCG_OK;
+    }
+    // full operators read and write both parities, the others even fields
+    const bool full = op == MSPCG_OP_D || op == MSPCG_OP_DDAG || op == MSPCG_OP_HOP ||
+                      op == MSPCG_OP_HOPDAG;
+    const bool with_B = op == MSPCG_OP_D || op == MSPCG_OP_MHAT || op == MSPCG_OP_A;
+    const bool prepare = op == MSPCG_OP_PREPARE;
+    const ToFull half{out, 0}, even{out, 1};
+    Field<S> none;
+    memset(&none, 0, sizeof(none));
+    Field<S> f[2] = {none, none}, t[2] = {none, none};  // by parity: the input, B (X) of it
+    f[0] = half_field<S>(c, pfx + "ap_ie", c->Nh);
+    if (!f[0].data) return MSPCG_ENOMEM;
+    if (full) f[1] = half_field<S>(c, pfx + "ap_io", c->Nh);
+    if (with_B) t[0] = half_field<S>(c, pfx + (full ? "ap_te" : "mh_t"), c->Nh);
+    if (op == MSPCG_OP_D || prepare) t[1] = half_field<S>(c, pfx + "ap_to", c->Nh);
+    if ((full && !f[1].data) || (with_B && !t[0].data) || ((op == MSPCG_OP_D || prepare) && !t[1].data))
+        return MSPCG_ENOMEM;
+    const CField<S> fe = cfield(f[0]), fo = cfield(f[1]);
+    T_(launch_pack_prog<S>(in, f, t, prepare ? P.X : P.B, c->act.mf, c->L, c->Ls, 0,
+                           full || prepare ? 2 : 1, st));
     switch (op) {
-        case MSPCG_OP_D: {
+        case MSPCG_OP_D:
             // D = M5op - (1/2) D_h B
-            Field<S> te = half_field<S>(c, pfx + "ap_te", c->Nh);
-            Field<S> to = half_field<S>(c, pfx + "ap_to", c->Nh);
-            T_(op_fived<S>(c, te, cfield(ie), P.B, nullptr, nullptr, st));
-            T_(op_fived<S>(c, to, cfield(io), P.B, nullptr, nullptr, st));
-            CField<S> ae = cfield(ie), ao = cfield(io);
-            T_(op_hop<S>(c, oe, cfield(to), 0, false, prog_scale(-0.5), &ae, P.M5, nullptr, nullptr, st));
-            T_(op_hop<S>(c, oo, cfield(te), 1, false, prog_scale(-0.5), &ao, P.M5, nullptr, nullptr, st));
+            T_(op_hop_ex<S>(c, none, cfield(t[1]), 0, false, prog_scale(-0.5), &fe, P.M5, nullptr,
+                            nullptr, nullptr, st, &half));
+            T_(op_hop_ex<S>(c, none, cfield(t[0]), 1, false, prog_scale(-0.5), &fo, P.M5, nullptr,
+                            nullptr, nullptr, st, &half));
             break;
-        }
-        case MSPCG_OP_DDAG: {
+        case MSPCG_OP_DDAG:
             // D^+ = M5op^+ - (1/2) B^+ Dd
-            CField<S> ae = cfield(ie), ao = cfield(io);
-            T_(op_hop<S>(c, oe, cfield(io), 0, true, scaled(P.Bdag, -0.5, -0.5), &ae, P.M5dag, nullptr, nullptr, st));
-            T_(op_hop<S>(c, oo, cfield(ie), 1, true, scaled(P.Bdag, -0.5, -0.5), &ao, P.M5dag, nullptr, nullptr, st));
+            T_(op_hop_ex<S>(c, none, fo, 0, true, scaled(P.Bdag, -0.5, -0.5), &fe, P.M5dag, nullptr,
+                            nullptr, nullptr, st, &half));
+            T_(op_hop_ex<S>(c, none, fe, 1, true, scaled(P.Bdag, -0.5, -0.5), &fo, P.M5dag, nullptr,
+                            nullptr, nullptr, st, &half));
             break;
-        }
         case MSPCG_OP_HOP:
         case MSPCG_OP_HOPDAG: {
             const bool dag = op == MSPCG_OP_HOPDAG;
-            T_(op_hop<S>(c, oe, cfield(io), 0, dag, P.id, nullptr, P.id, nullptr, nullptr, st));
-            T_(op_hop<S>(c, oo, cfield(ie), 1, dag, P.id, nullptr, P.id, nullptr, nullptr, st));
+            T_(op_hop_ex<S>(c, none, fo, 0, dag, P.id, nullptr, P.id, nullptr, nullptr, nullptr, st,
+                            &half));
+            T_(op_hop_ex<S>(c, none, fe, 1, dag, P.id, nullptr, P.id, nullptr, nullptr, nullptr, st,
+                            &half));
             break;
         }
-        case MSPCG_OP_M5INV:
-            T_(op_fived<S>(c, oe, cfield(ie), P.M5inv, nullptr, nullptr, st));
-            T_(op_fived<S>(c, oo, cfield(io), P.M5inv, nullptr, nullptr, st));
-            break;
         case MSPCG_OP_MHAT:
-            T_(op_mhat<S>(c, oe, cfield(ie), nullptr, nullptr, st));
+            T_(mhat_hops<S>(c, none, fe, cfield(t[0]), nullptr, nullptr, st, &even));
             break;
         case MSPCG_OP_MHATDAG:
-            T_(op_mhatdag<S>(c, oe, cfield(ie), nullptr, st));
+            T_(mhatdag_hops<S>(c, none, fe, nullptr, st, &even));
             break;
-        case MSPCG_OP_A:
-            T_(op_A<S>(c, oe, cfield(ie), nullptr, nullptr, st));
+        case MSPCG_OP_A: {
+            Field<S> y = half_field<S>(c, pfx + "A_y", c->Nh);
+            if (!y.data) return MSPCG_ENOMEM;
+            T_(mhat_hops<S>(c, y, fe, cfield(t[0]), nullptr, nullptr, st));
+            T_(mhatdag_hops<S>(c, none, cfield(y), nullptr, st, &even));
             break;
+        }
         case MSPCG_OP_PREPARE: {
             // b'_e = b_e + (1/2) D_h^eo X b_o ; bhat = Mhat^+ b'_e
-            Field<S> w = half_field<S>(c, pfx + "ap_to", c->Nh);
             Field<S> bp = half_field<S>(c, pfx + "ap_te", c->Nh);
-            CField<S> ae = cfield(ie);
-            T_(op_fived<S>(c, w, cfield(io), P.X, nullptr, nullptr, st));
-            T_(op_hop<S>(c, bp, cfield(w), 0, false, prog_scale(0.5), &ae, P.id, nullptr, nullptr, st));
-            T_(op_mhatdag<S>(c, oe, cfield(bp), nullptr, st));
+            if (!bp.data) return MSPCG_ENOMEM;
+            T_(op_hop<S>(c, bp, cfield(t[1]), 0, false, prog_scale(0.5), &fe, P.id, nullptr, nullptr, st));
+            T_(mhatdag_hops<S>(c, none, cfield(bp), nullptr, st, &even));
             break;
         }
         default:
             return MSPCG_EINVAL;
     }
-    const bool full_out = op == MSPCG_OP_D || op == MSPCG_OP_DDAG || op == MSPCG_OP_HOP ||
-                          op == MSPCG_OP_HOPDAG || op == MSPCG_OP_M5INV;
-    T_(launch_unpack_parity<S>(cfield(oe), out, c->L, c->Ls, 0, full_out ? 0 : 1, st));
-    if (full_out) T_(launch_unpack_parity<S>(cfield(oo), out, c->L, c->Ls, 1, 0, st));
 #undef T_
     return MSPCG_OK;
 }

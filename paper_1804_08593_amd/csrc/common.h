@@ -331,6 +331,63 @@ __device__ __forceinline__ long box_cb(const Box& b, const int c[4]) {
     return (long)(lex >> 1);
 }
 
+// Boundary fields (complex128 [Ls][V4][12]) are read and written through an LDS
+// array of 256 / LS sites: entry (site, component, s) at (site * 12 + component) *
+// (LS + 1) + s, so that the lanes of a site (consecutive s) and consecutive
+// components both hit distinct banks.  Global accesses then run along the 192
+// contiguous bytes of a (site, s).  lexs: each site's lex index (-1: none).
+template <typename T, int LS>
+__device__ __forceinline__ void load_boundary(cx<T>* lds, const int* lexs, const double2* full,
+                                              long V4) {
+    constexpr int SPB = 256 / LS, N = SPB * LS * 12, R = (N + 255) / 256;
+    nt_d2 v[R];  // every load in flight before the first is used
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int i = (int)threadIdx.x + 256 * k;
+        const int c = i % 12, r = i / 12, sl = r % SPB, s = r / SPB;
+        const int lex = i < N ? lexs[sl] : -1;
+        if (lex >= 0)
+            v[k] = __builtin_nontemporal_load(reinterpret_cast<const nt_d2*>(full) +
+                                              ((long)s * V4 + lex) * 12 + c);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int i = (int)threadIdx.x + 256 * k;
+        const int c = i % 12, r = i / 12, sl = r % SPB, s = r / SPB;
+        if (i < N) lds[(sl * 12 + c) * (LS + 1) + s] = {(T)v[k].x, (T)v[k].y};
+    }
+}
+// zero_other: the x partner (other parity) of each site gets zeros
+template <typename T, int LS>
+__device__ __forceinline__ void store_boundary(const cx<T>* lds, const int* lexs, double2* full,
+                                               long V4, int zero_other, int nthreads) {
+    constexpr int SPB = 256 / LS;
+    if (zero_other) {
+        for (int i = (int)threadIdx.x; i < SPB * LS * 24; i += nthreads) {
+            const int u = i % 24, r = i / 24, sl = r % SPB, s = r / SPB;
+            const int lex = lexs[sl];
+            if (lex < 0) continue;
+            const int odd = u >= 12, c = odd ? u - 12 : u;
+            nt_d2 v = {0.0, 0.0};
+            if (odd == (lex & 1)) {
+                const cx<T> t = lds[(sl * 12 + c) * (LS + 1) + s];
+                v = nt_d2{(double)t.re, (double)t.im};
+            }
+            put16<nt_d2, true>(reinterpret_cast<nt_d2*>(full) + ((long)s * V4 + (lex & ~1)) * 12 + u,
+                               v);
+        }
+    } else {
+        for (int i = (int)threadIdx.x; i < SPB * LS * 12; i += nthreads) {
+            const int c = i % 12, r = i / 12, sl = r % SPB, s = r / SPB;
+            const int lex = lexs[sl];
+            if (lex < 0) continue;
+            const cx<T> t = lds[(sl * 12 + c) * (LS + 1) + s];
+            put16<nt_d2, true>(reinterpret_cast<nt_d2*>(full) + ((long)s * V4 + lex) * 12 + c,
+                               nt_d2{(double)t.re, (double)t.im});
+        }
+    }
+}
+
 // Dense per-chirality 5D operators are applied as short programs of
 // elementary steps on the s-vector of one (site, component) (see fived.h).
 enum StepKind : int { STEP_NONE = 0, STEP_BIDI = 1, STEP_INV = 2 };

@@ -265,18 +265,17 @@ extern "C" int mspcg_force(mspcg_ctx* c, const void* X_dev, const void* Y_dev, v
     if (!c || !X_dev || !Y_dev || (!F_dev && !G_dev)) return MSPCG_EINVAL;
     if (!c->gauge) return MSPCG_ENOGAUGE;
     MSPCG_HIP(hipSetDevice(c->device));
-    Field<F64> xe = half_field<F64>(c, "d.fo_x", c->Nh);
     Field<F64> ye = half_field<F64>(c, "d.fo_y", c->Nh);
     Field<F64> be = half_field<F64>(c, "d.fo_be", c->Nh);
     Field<F64> bo = half_field<F64>(c, "d.fo_bo", c->Nh);
     Field<F64> ao = half_field<F64>(c, "d.fo_ao", c->Nh);
-    if (!xe.data || !ye.data || !be.data || !bo.data || !ao.data) return MSPCG_ENOMEM;
-    if (launch_pack_parity<F64>((const double2*)X_dev, xe, c->L, c->Ls, 0, st)) return MSPCG_EHIP;
-    if (launch_pack_parity<F64>((const double2*)Y_dev, ye, c->L, c->Ls, 0, st)) return MSPCG_EHIP;
+    if (!ye.data || !be.data || !bo.data || !ao.data) return MSPCG_ENOMEM;
     const Progs& P = c->pr;
     int e;
     // b = (B X, -(1/2) X D_h^oe B X) ; a = (Y, -(1/2) X^+ Dd^oe Y)
-    if ((e = op_fived<F64>(c, be, cfield(xe), P.B, nullptr, nullptr, st))) return e;
+    if (launch_pack_prog<F64>((const double2*)X_dev, nullptr, &be, P.B, c->act.mf, c->L, c->Ls, 0, 1, st))
+        return MSPCG_EHIP;
+    if (launch_pack_parity<F64>((const double2*)Y_dev, ye, c->L, c->Ls, 0, st)) return MSPCG_EHIP;
     if ((e = op_hop<F64>(c, bo, cfield(be), 1, false, scaled(P.X, -0.5, -0.5), nullptr, P.id,
                          nullptr, nullptr, st)))
         return e;

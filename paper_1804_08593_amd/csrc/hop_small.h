@@ -254,7 +254,16 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
             n2 = (double)t2;
         }
     } else if (c < 6 && active) {
-        if (!CG || a.cg_keep_out) {
+        if (!CG && a.bout) {
+            const long lex = 2 * cb + (gc[0] & 1);
+            double2* o = a.bout + ((long)s * a.V4 + lex) * 12 + c;
+            o[0] = make_double2(ru.re, ru.im);
+            o[6] = make_double2(rd.re, rd.im);
+            if (a.zero_other) {
+                o += lex & 1 ? -12 : 12;
+                o[0] = o[6] = make_double2(0.0, 0.0);
+            }
+        } else if (!CG || a.cg_keep_out) {
             store_comp<S>(a.out, obase, s, LS, c, ru);
             store_comp<S>(a.out, obase, s, LS, 6 + c, rd);
         }

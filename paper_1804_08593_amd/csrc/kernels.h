@@ -19,8 +19,21 @@ struct HopGeom {
 
 struct DevScalars;
 
+// Optional: the hop's result goes to a boundary field (complex128
+// [Ls][V4][12], see mspcg.h) instead of `out`, with zeros on the sites of the
+// other parity when zero_other.  Whole-lattice hops in FP64 and FP32 only; the
+// FP16 block hops' arguments stay without it (a larger argument block slows them).
 template <class S>
-struct HopArgs {
+struct HopBoundary {
+    double2* bout;
+    long V4;
+    int zero_other;
+};
+template <>
+struct HopBoundary<F16> {};
+
+template <class S>
+struct HopArgs : HopBoundary<S> {
     CField<S> in;
     Field<S> out;
     CField<S> aux;
@@ -127,6 +140,17 @@ long fived_grid_x(long Vh, int Ls);
 template <class S>
 int launch_pack_parity(const double2* full, Field<S> out, const int dims[4], int Ls, int par,
                        hipStream_t st);
+// The same for parities par0 .. par0 + npar - 1 (fields indexed from par0), with a
+// 5D program on the way: out[k] = the parity's field (data null: not stored),
+// t[k] = P of it (data null: not formed).
+template <class S>
+int launch_pack_prog(const double2* full, const Field<S>* out, const Field<S>* t,
+                     const FiveDProg& P, double mf, const int dims[4], int Ls, int par0, int npar,
+                     hipStream_t st);
+// full_out = P(full_in) on every site, boundary fields, arithmetic of S
+template <class S>
+int launch_prog_full(const double2* full_in, double2* full_out, const FiveDProg& P, double mf,
+                     const int dims[4], int Ls, hipStream_t st);
 template <class S>
 int launch_unpack_parity(CField<S> in, double2* full, const int dims[4], int Ls, int par,
                          int zero_other, hipStream_t st);

@@ -1,6 +1,7 @@
 // Layout conversion kernels: boundary (lexicographic complex128) fields to the
 // internal parity / domain layouts, link packing, and precision conversion.
 #include "common.h"
+#include "fived.h"
 #include "kernels.h"
 
 namespace mspcg {
@@ -39,44 +40,115 @@ __device__ __forceinline__ long cb_to_lex(long cb, int par, const Dims& d) {
     return lex_of(c, d.L);
 }
 
-template <class S>
-__global__ void pack_parity_kernel(const double2* full, Field<S> out, Dims d, int Ls, int par,
-                                   long V4, long Vh) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Vh * Ls) return;
-    const long cb = i / Ls;
-    const int s = (int)(i - cb * Ls);
-    const long lex = cb_to_lex(cb, par, d);
-    const double2* src = full + ((long)s * V4 + lex) * 12;
-    cx<typename S::real> v[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        const double2 t = src[c];
-        v[c] = {(typename S::real)t.x, (typename S::real)t.y};
+// lex index of each of the workgroup's sites (parity par, sites first, first + 1, ..)
+template <int SPB>
+__device__ __forceinline__ void site_lex(int* lexs, long first, long Vh, int par, const Dims& d) {
+    if ((int)threadIdx.x < SPB) {
+        const long cb = first + threadIdx.x;
+        lexs[threadIdx.x] = cb < Vh ? (int)cb_to_lex(cb, par, d) : -1;
     }
-    store_spinor<S>(out, i, v);
+}
+
+// the 5D program on the LDS array, one (site, component) chain per thread
+template <typename T, int LS>
+__device__ __forceinline__ void prog_lds(cx<T>* lds, const FiveDProg& P, T mf) {
+    constexpr int SPB = 256 / LS;
+    for (int ch = (int)threadIdx.x; ch < SPB * 12; ch += (int)blockDim.x) {
+        cx<T>* col = lds + ch * (LS + 1);
+        cx<T> v[LS];
+#pragma unroll
+        for (int t = 0; t < LS; ++t) v[t] = col[t];
+        apply_prog<LS, T>(P, ch % 12 < 6, mf, v);
+#pragma unroll
+        for (int t = 0; t < LS; ++t) col[t] = v[t];
+    }
 }
 
 template <class S>
-__global__ void unpack_parity_kernel(CField<S> in, double2* full, Dims d, int Ls, int par,
-                                     int zero_other, long V4, long Vh) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Vh * Ls) return;
-    const long cb = i / Ls;
-    const int s = (int)(i - cb * Ls);
-    const long lex = cb_to_lex(cb, par, d);
-    cx<typename S::real> v[12];
-    load_spinor<S>(in, i, v);
-    double2* dst = full + ((long)s * V4 + lex) * 12;
+struct PackArgs {
+    const double2* full;
+    Field<S> out[2], t[2];  // by parity - par0; data null: not wanted
+    FiveDProg p;
+    double mf;
+    Dims d;
+    int par0;
+    long V4, Vh;
+};
+
+// Boundary field -> internal parity fields, and a 5D program of them in the same
+// pass (blockIdx.y: parity).  Bound by HBM: one parity with B and both outputs at
+// 24^3x48x16 617 us, against 469 for the pack and 376 for the 5D kernel apart; the
+// pack alone at 16^3x32x12 59 us (67 with each thread reading its own 192 bytes; 84
+// with the LDS staging's loads waited for one by one).
+template <class S, int LS>
+__global__ __launch_bounds__(256) void pack_prog_kernel(PackArgs<S> a) {
+    using T = typename S::real;
+    constexpr int SPB = 256 / LS;
+    __shared__ __attribute__((aligned(16))) cx<T> lds[SPB * 12 * (LS + 1)];
+    __shared__ int lexs[SPB];
+    const int k = blockIdx.y, sl = threadIdx.x / LS, s = threadIdx.x - sl * LS;
+    const long first = (long)blockIdx.x * SPB;
+    site_lex<SPB>(lexs, first, a.Vh, a.par0 + k, a.d);
+    __syncthreads();
+    load_boundary<T, LS>(lds, lexs, a.full, a.V4);
+    __syncthreads();
+    const bool active = sl < SPB && first + sl < a.Vh;
+    const Field<S> out = k ? a.out[1] : a.out[0], t = k ? a.t[1] : a.t[0];
+    cx<T> v[12];
+    if (active && out.data) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) dst[c] = make_double2((double)v[c].re, (double)v[c].im);
-    if (zero_other) {
-        // the other-parity partner site in the same x pair is lex ^ 1
-        const long lex2 = lex ^ 1;
-        double2* d2 = full + ((long)s * V4 + lex2) * 12;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) d2[c] = make_double2(0.0, 0.0);
+        for (int c = 0; c < 12; ++c) v[c] = lds[(sl * 12 + c) * (LS + 1) + s];
+        store_spinor_at<S>(out, (first + sl) * LS, s, LS, v);
     }
+    if (!t.data) return;
+    __syncthreads();
+    prog_lds<T, LS>(lds, a.p, (T)a.mf);
+    __syncthreads();
+    if (active) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) v[c] = lds[(sl * 12 + c) * (LS + 1) + s];
+        store_spinor_at<S>(t, (first + sl) * LS, s, LS, v);
+    }
+}
+
+// P on every site of a boundary field (blockIdx.y: parity)
+template <class S, int LS>
+__global__ __launch_bounds__(256) void prog_full_kernel(const double2* in, double2* out,
+                                                        FiveDProg p, double mf, Dims d, long V4,
+                                                        long Vh) {
+    using T = typename S::real;
+    constexpr int SPB = 256 / LS;
+    __shared__ __attribute__((aligned(16))) cx<T> lds[SPB * 12 * (LS + 1)];
+    __shared__ int lexs[SPB];
+    site_lex<SPB>(lexs, (long)blockIdx.x * SPB, Vh, blockIdx.y, d);
+    __syncthreads();
+    load_boundary<T, LS>(lds, lexs, in, V4);
+    __syncthreads();
+    prog_lds<T, LS>(lds, p, (T)mf);
+    __syncthreads();
+    store_boundary<T, LS>(lds, lexs, out, V4, 0, (int)blockDim.x);
+}
+
+// Internal parity field -> boundary field.
+template <class S, int LS>
+__global__ __launch_bounds__(256) void unpack_parity_kernel(CField<S> in, double2* full, Dims d,
+                                                            int par, int zero_other, long V4,
+                                                            long Vh) {
+    using T = typename S::real;
+    constexpr int SPB = 256 / LS;
+    __shared__ __attribute__((aligned(16))) cx<T> lds[SPB * 12 * (LS + 1)];
+    __shared__ int lexs[SPB];
+    const int sl = threadIdx.x / LS, s = threadIdx.x - sl * LS;
+    const long first = (long)blockIdx.x * SPB;
+    site_lex<SPB>(lexs, first, Vh, par, d);
+    if (sl < SPB && first + sl < Vh) {
+        cx<T> v[12];
+        load_spinor_at<S, true>(in, (first + sl) * LS, s, LS, v);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) lds[(sl * 12 + c) * (LS + 1) + s] = v[c];
+    }
+    __syncthreads();
+    store_boundary<T, LS>(lds, lexs, full, V4, zero_other, (int)blockDim.x);
 }
 
 struct DomGrid {
@@ -264,13 +336,55 @@ int last_error() { return hipGetLastError() == hipSuccess ? 0 : -2; }
 }  // namespace
 
 template <class S>
+int launch_pack_prog(const double2* full, const Field<S>* out, const Field<S>* t,
+                     const FiveDProg& P, double mf, const int dims[4], int Ls, int par0, int npar,
+                     hipStream_t st) {
+    PackArgs<S> a = {};
+    a.full = full;
+    for (int k = 0; k < npar; ++k) {
+        if (out) a.out[k] = out[k];
+        if (t) a.t[k] = t[k];
+    }
+    a.p = P;
+    a.mf = mf;
+    a.d = Dims{{dims[0], dims[1], dims[2], dims[3]}};
+    a.par0 = par0;
+    a.V4 = (long)dims[0] * dims[1] * dims[2] * dims[3];
+    a.Vh = a.V4 / 2;
+    switch (Ls) {
+#define MSPCG_CASE(L)                                                                             \
+    case L:                                                                                       \
+        hipLaunchKernelGGL((pack_prog_kernel<S, L>), dim3(nblocks(a.Vh, 256 / L), npar), dim3(256), \
+                           0, st, a);                                                             \
+        break;
+        MSPCG_LS_LIST(MSPCG_CASE)
+#undef MSPCG_CASE
+        default: return -1;
+    }
+    return last_error();
+}
+
+template <class S>
 int launch_pack_parity(const double2* full, Field<S> out, const int dims[4], int Ls, int par,
                        hipStream_t st) {
+    return launch_pack_prog<S>(full, &out, nullptr, FiveDProg{}, 0.0, dims, Ls, par, 1, st);
+}
+
+template <class S>
+int launch_prog_full(const double2* full_in, double2* full_out, const FiveDProg& P, double mf,
+                     const int dims[4], int Ls, hipStream_t st) {
     Dims d{{dims[0], dims[1], dims[2], dims[3]}};
-    const long V4 = (long)dims[0] * dims[1] * dims[2] * dims[3];
-    const long Vh = V4 / 2;
-    hipLaunchKernelGGL(pack_parity_kernel<S>, dim3(nblocks(Vh * Ls, kThreads)), dim3(kThreads), 0,
-                       st, full, out, d, Ls, par, V4, Vh);
+    const long V4 = (long)dims[0] * dims[1] * dims[2] * dims[3], Vh = V4 / 2;
+    switch (Ls) {
+#define MSPCG_CASE(L)                                                                            \
+    case L:                                                                                      \
+        hipLaunchKernelGGL((prog_full_kernel<S, L>), dim3(nblocks(Vh, 256 / L), 2), dim3(256), 0, \
+                           st, full_in, full_out, P, mf, d, V4, Vh);                             \
+        break;
+        MSPCG_LS_LIST(MSPCG_CASE)
+#undef MSPCG_CASE
+        default: return -1;
+    }
     return last_error();
 }
 
@@ -280,8 +394,16 @@ int launch_unpack_parity(CField<S> in, double2* full, const int dims[4], int Ls,
     Dims d{{dims[0], dims[1], dims[2], dims[3]}};
     const long V4 = (long)dims[0] * dims[1] * dims[2] * dims[3];
     const long Vh = V4 / 2;
-    hipLaunchKernelGGL(unpack_parity_kernel<S>, dim3(nblocks(Vh * Ls, kThreads)), dim3(kThreads),
-                       0, st, in, full, d, Ls, par, zero_other, V4, Vh);
+    switch (Ls) {
+#define MSPCG_CASE(L)                                                                             \
+    case L:                                                                                       \
+        hipLaunchKernelGGL((unpack_parity_kernel<S, L>), dim3(nblocks(Vh, 256 / L)), dim3(256), 0, \
+                           st, in, full, d, par, zero_other, V4, Vh);                             \
+        break;
+        MSPCG_LS_LIST(MSPCG_CASE)
+#undef MSPCG_CASE
+        default: return -1;
+    }
     return last_error();
 }
 
@@ -352,11 +474,19 @@ int launch_convert(CField<SI> in, Field<SO> out, long n, hipStream_t st) {
     return last_error();
 }
 
-#define MSPCG_INST1(S)                                                                             \
+#define MSPCG_INST0(S)                                                                             \
+    template int launch_pack_prog<S>(const double2*, const Field<S>*, const Field<S>*,            \
+                                     const FiveDProg&, double, const int*, int, int, int,         \
+                                     hipStream_t);                                                 \
+    template int launch_prog_full<S>(const double2*, double2*, const FiveDProg&, double,          \
+                                     const int*, int, hipStream_t);                                \
     template int launch_pack_parity<S>(const double2*, Field<S>, const int*, int, int,            \
                                        hipStream_t);                                               \
     template int launch_unpack_parity<S>(CField<S>, double2*, const int*, int, int, int,          \
-                                         hipStream_t);                                             \
+                                         hipStream_t);
+MSPCG_INST0(F64)
+MSPCG_INST0(F32)
+#define MSPCG_INST1(S)                                                                             \
     template int launch_pack_links<S>(const double2*, typename S::elem*, const int*, const int*,  \
                                       const int*, const Box&, int, hipStream_t);
 MSPCG_INST1(F64)
