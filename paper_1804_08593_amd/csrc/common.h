@@ -14,11 +14,14 @@
 //     consecutive s, so every chunk access of a wave is contiguous, and a
 //     spinor costs K vector loads of 16 bytes per lane whatever the precision.
 //   * FP16 fields store value/scale as __half2 per complex component plus one
-//     FP32 scale per entry (the max |real| over its 24 reals), scale[i].
+//     FP32 scale per entry (the max |real| over its 24 reals), scale[i].  Their
+//     chunk k holds the four spins of colour k (FP64, FP32: components
+//     spin*3 + colour in order), one K chunk of the matrix-core hop.
 //   * Links are stored per output parity and link-box site as
 //     [parity][Vh_linkbox][8][9]: dirs 0..3 hold U_mu(x), dirs 4..7 hold
 //     U_mu(x-mu)^+ (already daggered), with the antiperiodic-time sign folded
-//     in.  The 72 entries of a site are contiguous so a workgroup stages them
+//     in (FP16: the forward and the backward entry of a direction side by side,
+//     see link_slot).  The 72 entries of a site are contiguous so a workgroup stages them
 //     with a few coalesced 16-byte loads and all Ls lanes reuse them.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -177,10 +180,10 @@ __device__ __forceinline__ void decode_raw(const RawSpinor<S>& r, cx<typename S:
         const float sc = apply_scale ? r.sc : 1.f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            v[4 * k + 0] = h2f(r.c[k].x, sc);
-            v[4 * k + 1] = h2f(r.c[k].y, sc);
-            v[4 * k + 2] = h2f(r.c[k].z, sc);
-            v[4 * k + 3] = h2f(r.c[k].w, sc);
+            v[k] = h2f(r.c[k].x, sc);
+            v[3 + k] = h2f(r.c[k].y, sc);
+            v[6 + k] = h2f(r.c[k].z, sc);
+            v[9 + k] = h2f(r.c[k].w, sc);
         }
     } else if constexpr (sizeof(typename S::real) == 8) {
 #pragma unroll
@@ -246,10 +249,10 @@ __device__ __forceinline__ void store_spinor_at(Field<S> f, long base, int s, in
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             nt_u4 t;
-            t.x = f2h(v[4 * k + 0].re * inv, v[4 * k + 0].im * inv);
-            t.y = f2h(v[4 * k + 1].re * inv, v[4 * k + 1].im * inv);
-            t.z = f2h(v[4 * k + 2].re * inv, v[4 * k + 2].im * inv);
-            t.w = f2h(v[4 * k + 3].re * inv, v[4 * k + 3].im * inv);
+            t.x = f2h(v[k].re * inv, v[k].im * inv);
+            t.y = f2h(v[3 + k].re * inv, v[3 + k].im * inv);
+            t.z = f2h(v[6 + k].re * inv, v[6 + k].im * inv);
+            t.w = f2h(v[9 + k].re * inv, v[9 + k].im * inv);
             put16<nt_u4, NT>(p + (long)k * ls, t);
         }
     } else if constexpr (sizeof(typename S::real) == 8) {
@@ -269,6 +272,12 @@ template <class S, bool NT = false>
 __device__ __forceinline__ void store_spinor(Field<S> f, long i, const cx<typename S::real> (&v)[12]) {
     const int s = entry_lane(i, f.ls);
     store_spinor_at<S, NT>(f, i - s, s, f.ls, v);
+}
+
+// place of entry k (3 row + column) of direction dir among a site's 72 link entries
+template <class S>
+__host__ __device__ constexpr int link_slot(int dir, int k) {
+    return S::has_scale ? ((dir & 3) * 9 + k) * 2 + (dir >> 2) : dir * 9 + k;
 }
 
 template <class S, bool NT = false>

@@ -6,7 +6,8 @@ namespace mspcg {
 
 MSPCG_HOP_WIDE(MSPCG_HOP_EXTERN, F16)
 
-template int launch_hop<F16>(const HopArgs<F16>&, int, int, bool, bool, hipStream_t);
+template int launch_hop<F16>(const HopArgs<F16>&, int, int, bool, bool, hipStream_t,
+                             const HopReach*);
 
 long hop_grid_x(long Vh, int Ls, int ndom, bool small) {
     const int spb = small && hop_is_small(Vh, Ls, ndom) ? 64 / Ls : 256 / Ls;

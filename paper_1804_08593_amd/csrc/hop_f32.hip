@@ -6,7 +6,8 @@ namespace mspcg {
 
 MSPCG_HOP_WIDE(MSPCG_HOP_EXTERN, F32)
 
-template int launch_hop<F32>(const HopArgs<F32>&, int, int, bool, bool, hipStream_t);
+template int launch_hop<F32>(const HopArgs<F32>&, int, int, bool, bool, hipStream_t,
+                             const HopReach*);
 template int launch_multi_hop<F32>(const MultiHop<F32>*, long, int, bool, bool, bool,
                                     bool, hipStream_t);
 

@@ -30,8 +30,7 @@
 #endif
 // MSPCG_HOP_PF{64,32,16}: directions whose raw neighbour spinors are loaded
 // before any of them is decoded and applied (per storage precision).  Two
-// for FP16 (12^3x24 domain hop 428 -> 415 us; with the packed-FP16 products
-// 396 -> 385 us, four: 413 us); deeper groups did not help the FP64 and FP32
+// for FP16 (12^3x24 domain hop at Ls = 16 428 -> 415 us); deeper groups did not help the FP64 and FP32
 // hops.
 #ifndef MSPCG_HOP_PF64
 #define MSPCG_HOP_PF64 1
@@ -41,27 +40,6 @@
 #endif
 #ifndef MSPCG_HOP_PF16
 #define MSPCG_HOP_PF16 2
-#endif
-// MSPCG_HOP_MFMA: FP16-storage hops at Ls = 16 multiply links by spinors on
-// the matrix cores (see hop_body).  Off by default: the hop is bound by HBM
-// and LDS traffic, not by its 1320 flops per 5D site, and the operand staging
-// the matrix-core form needs made the 12^3x24 domain hop 11% slower (463 us
-// against 416 us) on MI355X.  Build with -DMSPCG_HOP_MFMA=1 to select it.
-#ifndef MSPCG_HOP_MFMA
-#define MSPCG_HOP_MFMA 0
-#endif
-// MSPCG_HOP_PK16: FP16-storage hops project and multiply by the link in
-// packed FP16 arithmetic (two halves per instruction, see dir_apply_pk) and
-// accumulate the directions in FP32.  It cuts the Ls = 16 block hop's VALU
-// instructions by a sixth (2007 -> 1670 in the kernel body) and its time by
-// 6% on MI355X (12^3x24 domains: 429 -> 403 us), with unchanged outer
-// iteration counts.  Off by default: the local solves keep FP32 arithmetic
-// on their FP16-stored operands; build with -DMSPCG_HOP_PK16=1 to select it.
-#ifndef MSPCG_HOP_PK16
-#define MSPCG_HOP_PK16 0
-#endif
-#ifndef MSPCG_HOP_MFMA_WAVES
-#define MSPCG_HOP_MFMA_WAVES 4
 #endif
 
 namespace mspcg {
@@ -157,62 +135,6 @@ __device__ __forceinline__ void dir_apply(const cx<typename S::real> (&p)[12],
             cfma(t, u[i * 3 + 1], h[sp * 3 + 1]);
             cfma(t, u[i * 3 + 2], h[sp * 3 + 2]);
             w[sp * 3 + i] = t;
-        }
-    reconstruct<MU, SIG>(w, acc, k);
-}
-
-typedef _Float16 pk_h2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ pk_h2 pk_bits(unsigned v) { return __builtin_bit_cast(pk_h2, v); }
-__device__ __forceinline__ pk_h2 pk_bcast(_Float16 v) { return pk_h2{v, v}; }
-__device__ __forceinline__ pk_h2 pk_itimes(pk_h2 v) { return pk_h2{-v.y, v.x}; }  // i v
-template <int SIG>
-__device__ __forceinline__ pk_h2 pk_addsig(pk_h2 a, pk_h2 b) {  // a + SIG b
-    if constexpr (SIG > 0)
-        return a + b;
-    else
-        return a - b;
-}
-
-// acc += k (1 + SIG g_mu) U p on FP16 storage in packed FP16 arithmetic: p
-// (the stored neighbour, scaled to max |real| <= 1) and U (|U_ij| <= 1) stay
-// FP16, the projection is one packed add and each complex multiply-add two
-// packed FMAs per (Re, Im) pair; the products w = U h are widened to FP32 in
-// the reconstruct, where the neighbour's scale k multiplies them.
-template <int MU, int SIG>
-__device__ __forceinline__ void dir_apply_pk(const pk_h2 (&p)[12], const pk_h2 (&u)[9],
-                                             cx<float> (&acc)[12], float k) {
-    pk_h2 h[6];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const pk_h2 u0 = p[c], u1 = p[3 + c], d0 = p[6 + c], d1 = p[9 + c];
-        if constexpr (MU == 0) {  // e d = (-i d1, -i d0)
-            h[c] = pk_addsig<-SIG>(u0, pk_itimes(d1));
-            h[3 + c] = pk_addsig<-SIG>(u1, pk_itimes(d0));
-        } else if constexpr (MU == 1) {  // e d = (-d1, d0)
-            h[c] = pk_addsig<-SIG>(u0, d1);
-            h[3 + c] = pk_addsig<SIG>(u1, d0);
-        } else if constexpr (MU == 2) {  // e d = (-i d0, i d1)
-            h[c] = pk_addsig<-SIG>(u0, pk_itimes(d0));
-            h[3 + c] = pk_addsig<SIG>(u1, pk_itimes(d1));
-        } else {  // e d = d
-            h[c] = pk_addsig<SIG>(u0, d0);
-            h[3 + c] = pk_addsig<SIG>(u1, d1);
-        }
-    }
-    cx<float> w[6];
-#pragma unroll
-    for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            pk_h2 t = pk_bcast(u[i * 3].x) * h[sp * 3];
-            t = __builtin_elementwise_fma(pk_bcast(u[i * 3].y), pk_itimes(h[sp * 3]), t);
-#pragma unroll
-            for (int j = 1; j < 3; ++j) {
-                t = __builtin_elementwise_fma(pk_bcast(u[i * 3 + j].x), h[sp * 3 + j], t);
-                t = __builtin_elementwise_fma(pk_bcast(u[i * 3 + j].y), pk_itimes(h[sp * 3 + j]), t);
-            }
-            w[sp * 3 + i] = {(float)t.x, (float)t.y};
         }
     reconstruct<MU, SIG>(w, acc, k);
 }
@@ -331,8 +253,6 @@ __device__ __forceinline__ void sfor(F&& f) {
 // arithmetic, not memory, sets the pace)
 template <class S, int LS, bool EPA, bool CG>
 constexpr int hop_min_waves() {
-    // the matrix-core variant (FP16, Ls = 16) fits 128 VGPRs
-    if (S::has_scale && LS == 16 && MSPCG_HOP_MFMA) return MSPCG_HOP_MFMA_WAVES;
     return (S::has_scale && !EPA && !CG && LS == 8) ? 6 : MSPCG_HOP_MINWAVES;
 }
 
@@ -357,61 +277,17 @@ struct HopShape {
     // entry (site, s, c) at (site * 12 + c) * LSP + s, so the lanes of a site
     // (consecutive s) and the chain threads (consecutive c) both hit distinct banks
     static constexpr int LSP = LS + 1;
-    // FP16 links are decoded to FP32 once, when staged (kept FP16 for the
-    // packed-FP16 products); LE is the LDS entry
-    static constexpr bool PK = S::has_scale && MSPCG_HOP_PK16 && !(LS == 16 && MSPCG_HOP_MFMA);
-    using LE = typename std::conditional<S::has_scale && !PK, nt_f2, E>::type;
+    // FP16 links are decoded to FP32 once, when staged; LE is the LDS entry
+    using LE = typename std::conditional<S::has_scale, nt_f2, E>::type;
     static constexpr int NCH = 72 * (int)sizeof(E) / 16;   // 16-byte chunks of one site's links
     static constexpr int LSTR = 72 * (int)sizeof(LE) / 16 + 1;  // padded LDS site stride (chunks)
     static constexpr bool LDSL = SPB * LSTR * 16 <= 40 * 1024;
     // the s-exchange array serves both the chain programs (EPH/EPA) and the
     // single-step programs applied by neighbour exchange
     static constexpr int EPI_BYTES = SPB * 12 * LSP * (int)sizeof(cx<T>);
-    // FP16 storage at Ls = 16 (a wave = 4 sites x 16 s): the SU(3) products
-    // run as v_mfma_f32_16x16x32_f16 with the links staged in LDS as operand
-    // rows (1 KB per site) and a 16-byte zero row
-    static constexpr bool MF = S::has_scale && LS == 16 && MSPCG_HOP_MFMA;
-    static constexpr int MF_SITE = 1024;
-    static constexpr int LNK_BYTES = MF ? SPB * MF_SITE + 16 : (LDSL ? SPB * LSTR * 16 : 16);
+    static constexpr int LNK_BYTES = LDSL ? SPB * LSTR * 16 : 16;
     static constexpr int LDS_BYTES = EPI_BYTES > LNK_BYTES ? EPI_BYTES : LNK_BYTES;
 };
-
-typedef _Float16 mf_half8 __attribute__((ext_vector_type(8)));
-typedef float mf_float4 __attribute__((ext_vector_type(4)));
-
-// One 16-byte operand row of the matrix-core link product: for link row i
-// (entries u_i0..u_i2), op 0 gives [Re u, 0, -Im u, 0] and op 1 [Im u, 0, Re u, 0],
-// so that with a spinor colour vector packed as [Re psi, 0, Im psi, 0] the
-// products give Re(U psi)_i and Im(U psi)_i (FP16 inputs, exact products,
-// FP32 accumulation).
-__device__ __forceinline__ nt_u4 mf_link_row(const unsigned (&e)[3], int op) {
-    // e[j]: __half2 (Re, Im) of u_ij as a 32-bit word
-    const unsigned re01 = (e[0] & 0xffffu) | (e[1] << 16);
-    const unsigned im01 = (e[0] >> 16) | (e[1] & 0xffff0000u);
-    const unsigned re2 = e[2] & 0xffffu, im2 = e[2] >> 16;
-    if (op == 0)  // [Re u0, Re u1, Re u2, 0, -Im u0, -Im u1, -Im u2, 0]
-        return nt_u4{re01, re2, im01 ^ 0x80008000u, im2 ^ 0x8000u};
-    return nt_u4{im01, im2, re01, re2};
-}
-
-// Spin component sp of a raw FP16 spinor (unscaled) packed as an MFMA B
-// operand: [Re c0, Re c1, Re c2, 0, Im c0, Im c1, Im c2, 0] for the colours
-// of that spin.
-__device__ __forceinline__ mf_half8 mf_spin_operand(const RawSpinor<F16>& r, int sp) {
-    unsigned w[12];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        w[4 * k + 0] = r.c[k].x;
-        w[4 * k + 1] = r.c[k].y;
-        w[4 * k + 2] = r.c[k].z;
-        w[4 * k + 3] = r.c[k].w;
-    }
-    const unsigned w0 = w[3 * sp], w1 = w[3 * sp + 1], w2 = w[3 * sp + 2];
-    // byte selects: low halves of w0, w1 (the real parts), high halves (imaginary)
-    const nt_u4 v{__builtin_amdgcn_perm(w1, w0, 0x05040100u), w2 & 0xffffu,
-                  __builtin_amdgcn_perm(w1, w0, 0x07060302u), w2 >> 16};
-    return __builtin_bit_cast(mf_half8, v);
-}
 
 template <int LS>
 constexpr int SPB_THREADS() {
@@ -482,21 +358,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<S>& a, int bx, int d, int
         for (int m = 0; m < 4; ++m) lc[m] = gc[m] - g.link.off[m];
         gl = a.links + (long)d * a.link_dom_stride +
              ((long)g.out_par * g.link.Vh + box_cb(g.link, lc)) * 72;
-        if constexpr (SH::MF) {
-            // 64 operand rows per site (direction, op, row i), i = 3 zero
-            const unsigned* src = reinterpret_cast<const unsigned*>(gl);
-            for (int r = s; r < 64; r += LS) {
-                const int dir = r >> 3, op = (r >> 2) & 1, i = r & 3;
-                nt_u4 v{0u, 0u, 0u, 0u};
-                if (i < 3) {
-                    unsigned e[3];
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) e[j] = src[dir * 9 + i * 3 + j];
-                    v = mf_link_row(e, op);
-                }
-                *reinterpret_cast<nt_u4*>(smem + sl * SH::MF_SITE + r * 16) = v;
-            }
-        } else if constexpr (LDSL) {
+        if constexpr (LDSL) {
             const nt_u4* src = reinterpret_cast<const nt_u4*>(gl);
             for (int j = s; j < NCH; j += LS) {
                 nt_u4 v;
@@ -504,9 +366,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<S>& a, int bx, int d, int
                     v = __builtin_nontemporal_load(src + j);
                 else
                     v = src[j];
-                if constexpr (SH::PK) {
-                    lnk[sl * LSTR + j] = v;
-                } else if constexpr (S::has_scale) {
+                if constexpr (S::has_scale) {
                     const cx<float> e0 = h2f(v.x, 1.f), e1 = h2f(v.y, 1.f);
                     const cx<float> e2 = h2f(v.z, 1.f), e3 = h2f(v.w, 1.f);
                     nt_f4* dst = reinterpret_cast<nt_f4*>(lnk + sl * LSTR + 2 * j);
@@ -518,89 +378,13 @@ __device__ __forceinline__ void hop_body(const HopArgs<S>& a, int bx, int d, int
             }
         }
     }
-    if constexpr (SH::MF) {
-        // sites without output (beyond the box or list) get zero operand rows,
-        // so no stale LDS value enters a matrix product
-        if (!active && sl < SPB)
-            for (int r = s; r < 64; r += LS)
-                *reinterpret_cast<nt_u4*>(smem + sl * SH::MF_SITE + r * 16) = nt_u4{0u, 0u, 0u, 0u};
-        if (threadIdx.x == 0)
-            *reinterpret_cast<nt_u4*>(smem + SPB * SH::MF_SITE) = nt_u4{0u, 0u, 0u, 0u};
-        __syncthreads();
-    } else if constexpr (LDSL) {
-        __syncthreads();
-    }
+    if constexpr (LDSL) __syncthreads();
 
     constexpr int KC = Chunk<S>::K;
     cx<T> acc[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
-    if constexpr (SH::MF) {
-        // Every lane of the wave takes part in the matrix products (lanes
-        // without an output or a neighbour use zero operands).  The wave's 4
-        // sites x 16 s are the 16 columns (s) and the 4 blocks of 4 rows
-        // (site, colour row i) of a 16x16x32 product whose A operand is
-        // block-diagonal: lane L holds row L%16 = (site gm, row im) against
-        // the K block L/16 = site gk, nonzero only when gm == gk.
-        const long ibase = (long)d * g.in.Vh;
-        const InPos ip = in_position(g, gc);
-        gchar* in_d = uniform_ptr(reinterpret_cast<const char*>(a.in.data) + ibase * LS * KC * 16);
-        gchar* sc_d = uniform_ptr(reinterpret_cast<const char*>(a.in.scale + ibase * LS));
-        const unsigned s16 = (unsigned)s * 16u, s4 = (unsigned)s * 4u;
-        const int L = (int)(threadIdx.x & 63), wv = (int)(threadIdx.x >> 6);
-        const int gm = (L & 15) >> 2, im = L & 3, gk = L >> 4;
-        const unsigned char* arow = (gm == gk) ? smem + (4 * wv + gm) * SH::MF_SITE + im * 16
-                                               : smem + SPB * SH::MF_SITE;
-        const int astep = (gm == gk) ? 64 : 0;  // bytes between the op-row groups of a direction
-        constexpr int SF = DAG ? 1 : -1;
-        constexpr int SB = -SF;
-        sfor<8>([&](auto di) {
-            constexpr int D = decltype(di)::value;
-            constexpr int MU = D / 2;
-            constexpr bool FWD = (D % 2) == 0;
-            long n = 0;
-            const bool ok = active && neighbour<MU, FWD ? 1 : 0>(g, ip, n);
-            // a dropped hop (or a lane without output) reads the box's first
-            // site, finite data, and weighs it by zero: no branch around the
-            // loads, and no undefined value enters the matrix product
-            const unsigned un = ok ? (unsigned)n : 0u;
-            RawSpinor<S> raw;
-            gchar* pb = in_d + (unsigned long)((unsigned)__umul24(un, LS * KC * 16) + s16);
-#pragma unroll
-            for (int k = 0; k < KC; ++k)
-                raw.c[k] = *reinterpret_cast<const __attribute__((address_space(1))) nt_u4*>(
-                    pb + k * LS * 16);
-            const float scn = *reinterpret_cast<const __attribute__((address_space(1))) float*>(
-                sc_d + (unsigned long)((unsigned)__umul24(un, LS * 4) + s4));
-            raw.sc = ok ? scn : 0.f;
-            constexpr int LDIR = FWD ? MU : 4 + MU;  // link slot of this direction
-            const mf_half8 are =
-                *reinterpret_cast<const mf_half8*>(arow + astep * (2 * LDIR));
-            const mf_half8 aim =
-                *reinterpret_cast<const mf_half8*>(arow + astep * (2 * LDIR + 1));
-            cx<float> up[12];
-#pragma unroll
-            for (int sp = 0; sp < 4; ++sp) {
-                const mf_half8 b = mf_spin_operand(raw, sp);
-                const mf_float4 z = {0.f, 0.f, 0.f, 0.f};
-                const mf_float4 dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(are, b, z, 0, 0, 0);
-                const mf_float4 dm = __builtin_amdgcn_mfma_f32_16x16x32_f16(aim, b, z, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) up[sp * 3 + i] = {dr[i], dm[i]};
-            }
-            // (1 + sig g_mu) U psi = U (1 + sig g_mu) psi: project the products
-            cx<float> h[6];
-            project<MU, FWD ? SF : SB, false>(up, h, 1.f);
-            reconstruct<MU, FWD ? SF : SB>(h, acc, raw.sc);
-            // finish this direction here: the empty asm pins the accumulators
-            // (so the products are not kept live and folded in at the end)
-            // and the scheduling barrier keeps the next direction's loads
-            // below; both cost less than the registers they save
-#pragma unroll
-            for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[c].re), "+v"(acc[c].im));
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    } else if (active) {
+    if (active) {
         const long ibase = (long)d * g.in.Vh;
         const InPos ip = in_position(g, gc);
         // the domain's input box (a workgroup-uniform base, kept in scalar
@@ -649,34 +433,21 @@ __device__ __forceinline__ void hop_body(const HopArgs<S>& a, int bx, int d, int
                 constexpr int D = G0 + decltype(j)::value;
                 constexpr int MU = D / 2;
                 constexpr bool FWD = (D % 2) == 0;
-                constexpr int LD = (FWD ? MU : 4 + MU) * 9;  // first entry of this link
-                if constexpr (SH::PK) {
-                    static_assert(LDSL, "packed-FP16 hops read their links from LDS");
-                    if (ok[j]) {
-                        pk_h2 p[12], u[9];
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) {
-                            p[4 * q + 0] = pk_bits(raw[j].c[q].x);
-                            p[4 * q + 1] = pk_bits(raw[j].c[q].y);
-                            p[4 * q + 2] = pk_bits(raw[j].c[q].z);
-                            p[4 * q + 3] = pk_bits(raw[j].c[q].w);
-                        }
-                        const unsigned* le = reinterpret_cast<const unsigned*>(lnk + sl * LSTR) + LD;
-#pragma unroll
-                        for (int q = 0; q < 9; ++q) u[q] = pk_bits(le[q]);
-                        dir_apply_pk<MU, FWD ? SF : SB>(p, u, acc, raw[j].sc);
-                    }
-                } else if (ok[j]) {
+                constexpr int DIR = FWD ? MU : 4 + MU;
+                if (ok[j]) {
                     cx<T> p[12];
                     decode_raw<S>(raw[j], p, false);
                     cx<T> u[9];
                     if constexpr (LDSL) {
-                        const LE* le = reinterpret_cast<const LE*>(lnk + sl * LSTR) + LD;
+                        const LE* le = reinterpret_cast<const LE*>(lnk + sl * LSTR);
 #pragma unroll
-                        for (int k = 0; k < 9; ++k) u[k] = {(T)le[k].x, (T)le[k].y};
+                        for (int k = 0; k < 9; ++k) {
+                            const LE t = le[link_slot<S>(DIR, k)];
+                            u[k] = {(T)t.x, (T)t.y};
+                        }
                     } else {
 #pragma unroll
-                        for (int k = 0; k < 9; ++k) u[k] = load_link<S, MSPCG_HOP_NT>(gl + LD + k);
+                        for (int k = 0; k < 9; ++k) u[k] = load_link<S, MSPCG_HOP_NT>(gl + link_slot<S>(DIR, k));
                     }
                     const T k = S::has_scale ? (T)raw[j].sc : (T)1;
                     dir_apply<S, MU, FWD ? SF : SB>(p, u, acc, k, one);
@@ -925,7 +696,8 @@ void launch_ls(const HopArgs<S>& a, int ndom, bool dag, hipStream_t st) {
     extern template void launch_ls<S, L>(const HopArgs<S>&, int, bool, hipStream_t);
 
 template <class S>
-int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipStream_t st) {
+int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipStream_t st,
+               const HopReach* reach) {
     if (a.cg_r.data && (!dag || !a.partials)) return -1;
     // FP16-storage hops address a domain's input sites with 32-bit offsets
     const long site_bytes = (long)Ls * Chunk<S>::K * 16;
@@ -933,6 +705,12 @@ int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipS
     if (small && hop_is_small(a.site_list ? a.n_list : a.g.out.Vh, Ls, ndom)) {
         if (launch_hop_small<S>(a, Ls, ndom, dag, st)) return -1;
         return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+    if constexpr (S::has_scale) {
+        if (reach && hop_is_rows<S>(a.site_list ? a.n_list : a.g.out.Vh, reach->widest, Ls, ndom)) {
+            if (launch_hop_rows(a, Ls, ndom, dag, *reach, st)) return -1;
+            return hipGetLastError() == hipSuccess ? 0 : -2;
+        }
     }
     switch (Ls) {
 #define MSPCG_CASE(L) \

@@ -21,6 +21,7 @@ constexpr int kSmallThreads = 512;
 template <class S>
 __device__ __forceinline__ long comp_index(long base, int s, int ls, int c) {
     constexpr int V = Chunk<S>::V, K = Chunk<S>::K;
+    if constexpr (S::has_scale) return (base * K + (long)(c % 3) * ls + s) * V + c / 3;
     return (base * K + (long)(c / V) * ls + s) * V + c % V;
 }
 template <class S>
@@ -110,11 +111,10 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
 #pragma unroll
                 for (int m = 0; m < 4; ++m) lc[m] = gc[m] - g.link.off[m];
                 const E* gl = a.links + (long)d * a.link_dom_stride +
-                              ((long)g.out_par * g.link.Vh + box_cb(g.link, lc)) * 72 +
-                              (FWD ? MU : 4 + MU) * 9;
+                              ((long)g.out_par * g.link.Vh + box_cb(g.link, lc)) * 72;
                 cx<T> u[9];
 #pragma unroll
-                for (int q = 0; q < 9; ++q) u[q] = load_link<S>(gl + q);
+                for (int q = 0; q < 9; ++q) u[q] = load_link<S>(gl + link_slot<S>(FWD ? MU : 4 + MU, q));
                 cx<T> p[12], h[6];
                 decode_raw<S>(raw, p, false);
                 project<MU, FWD ? SF : SB, false>(p, h, (T)1);

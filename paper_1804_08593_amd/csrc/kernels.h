@@ -68,9 +68,80 @@ struct HopArgs : HopBoundary<S> {
     long n_list;
 };
 
-// small: the small-launch kernel (hop_small.h) may be used
+// A FiveDProg as the FP16 matrix-core hop reads it, in single precision: with
+// K (the plain hop) (1 - q K)^-1 then 1 + a K, with K^+ (the dagger hop) the
+// reverse order, each where present.
+struct RowProg {
+    int bidi, inv;
+    float a, corner;  // corner: -mf a
+    float q, cinv;    // cinv: -mf / (1 + mf q^Ls)
+    float su, sd;
+};
+// false: the program has a form that RowProg does not hold
+inline bool row_prog_of(const FiveDProg& p, bool dag, double mf, int Ls, RowProg& r) {
+    r = RowProg{};
+    for (int k = 0; k < p.nsteps; ++k) {
+        if ((p.dag[k] != 0) != dag) return false;
+        if (p.kind[k] == STEP_BIDI) {
+            if (r.bidi || (dag && r.inv)) return false;
+            r.bidi = 1;
+            r.a = (float)p.a[k];
+            r.corner = (float)-(p.a[k] * mf);
+        } else {
+            if (r.inv || (!dag && r.bidi)) return false;
+            r.inv = 1;
+            double qL = 1;
+            for (int s = 0; s < Ls; ++s) qL *= p.a[k];
+            r.q = (float)p.a[k];
+            r.cinv = (float)(-mf / (1.0 + mf * qL));
+        }
+    }
+    r.su = (float)p.scale[0];
+    r.sd = (float)p.scale[1];
+    return true;
+}
+
+// Which of a block hop's output sites matter: those within `dist` sites (Manhattan
+// distance) of the block of extent blk (0: not cut) at the domain origin; every one
+// when dist < 0.
+struct HopReach {
+    long widest;  // sites of the largest box of a domain
+    int dist, blk[4];
+};
+
+// Arguments of the FP16 matrix-core hop (hop_rows.h), from HopArgs.
+struct RowArgs {
+    CField<F16> in, aux, cg_p;
+    Field<F16> out, cg_r, cg_x;
+    const __half2* links;
+    long link_dom_stride;
+    HopGeom g;
+    RowProg rh, ra;
+    int has_aux, chunk, reach, blk[4], xcd_remap, cg_first;
+    double* partials;
+    const int* done;
+    const DevScalars* cg_sc;
+    const double* cg_alpha;
+};
+
+// x extent of a strip piece of the FP16 matrix-core hop.  A piece loads two
+// slices of inputs beyond its own, so it has at least 4 steps where the box
+// does; 6144 pieces are two rounds of the 3 waves per SIMD that its
+// registers allow, so that the last round costs little.
+inline int row_chunk(const Box& out, int ndom) {
+    const long strips = (long)out.E[1] * out.E[2] * out.E[3] / 8 * ndom;
+    int n = out.E[0];
+    while (n > 4 && strips * ((out.E[0] + n - 1) / n) < 6144) n = (n / 2 + 1) & ~1;
+    return n;
+}
+
+// small: hop_is_small launches take the small-launch kernel (hop_small.h); reach
+// (FP16 block hops): hop_is_rows launches take the matrix-core kernel
 template <class S>
-int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipStream_t st);
+int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipStream_t st,
+               const HopReach* reach = nullptr);
+int launch_hop_rows(const HopArgs<F16>& a, int Ls, int ndom, bool dag, const HopReach& reach,
+                    hipStream_t st);
 template <class S>
 int launch_hop_small(const HopArgs<S>& a, int Ls, int ndom, bool dag, hipStream_t st);
 
@@ -106,6 +177,26 @@ long hop_grid_x(long Vh, int Ls, int ndom, bool small);
 // 75, 8^3x16x8 (32768) 99 / 73, 8^4x24 (49152) 97 / 138, 8^3x16x16 (65536) 102 /
 // 112, 12^4x8 (82944) 137 / 142, 12^4x12 156 / 188.
 inline bool hop_is_small(long Vh, int Ls, int ndom) { return Vh * Ls * ndom <= 42000; }
+
+// Whether an FP16 block hop onto Vh sites of each of ndom domains takes the
+// matrix-core kernel, and its workgroups per domain.  Ls = 16 fills the columns
+// of its matrix instruction (with Ls = 12 in them, 24^4 in 12^4 blocks, six local
+// steps took 6138 us against the general kernel's 5657).  It needs enough sites
+// for strips of some length on every wave slot: 16^3 x 32 (65536 sites) in 8^3 x 16
+// blocks 3177 against 2999 us, 24^4 (165888) in 12^4 blocks 6701 against 6763, in
+// two 24 x 24 x 12 x 24 blocks 5353 against 5536, 24^3 x 48 (331776) in two blocks
+// 10491 against 11178.  A field's part of the largest box (`widest` sites) stays
+// below the reach of its 32-bit offsets.
+template <class S>
+inline bool hop_is_rows(long Vh, long widest, int Ls, int ndom) {
+    return S::has_scale && Ls == 16 && Vh * ndom >= 150000 && widest * Ls * 48 < 0x70000000;
+}
+constexpr int kRowWaves = 4;  // waves (strip pieces) of a workgroup
+inline long row_grid_x(const Box& out, int ndom) {
+    const int n = row_chunk(out, ndom);
+    const long pieces = (long)out.E[1] * out.E[2] * out.E[3] / 8 * ((out.E[0] + n - 1) / n);
+    return (pieces + kRowWaves - 1) / kRowWaves;
+}
 
 // out = P(in) on one box per domain (optionally |out|^2 partials).
 template <class S>

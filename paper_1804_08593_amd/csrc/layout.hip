@@ -294,7 +294,7 @@ __global__ void pack_links_kernel(const double2* U, typename S::elem* out, DomGr
         sign = -1.0;
     }
     const double2* u = U + ((long)mu * V4 + lex_of(y, g.L)) * 9;
-    const long obase = (long)d * (2 * 72 * lb.Vh) + ((long)par * lb.Vh + cb) * 72 + dir * 9;
+    const long obase = (long)d * (2 * 72 * lb.Vh) + ((long)par * lb.Vh + cb) * 72;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
         const int row = k / 3, col = k % 3;
@@ -313,7 +313,7 @@ __global__ void pack_links_kernel(const double2* U, typename S::elem* out, DomGr
             e.x = (typename S::real)v.x;
             e.y = (typename S::real)v.y;
         }
-        out[obase + k] = e;
+        out[obase + link_slot<S>(dir, k)] = e;
     }
 }
 

@@ -318,6 +318,24 @@ static double hop_read_sites(const Box& in, const Box& out) {
     return n;
 }
 
+static HopReach hop_reach(const Domains& D, const int* list) {
+    HopReach r;
+    r.widest = D.pad2.Vh;
+    r.dist = !list ? -1 : (list == D.list_y ? 2 : 1);
+    for (int m = 0; m < 4; ++m) r.blk[m] = D.nb[m] > 1 ? D.blk[m] : 0;
+    return r;
+}
+
+// workgroups per domain of a block hop onto box `out` (nlist > 0: onto nlist of
+// its sites); alt: the small-launch and matrix-core kernels may be used
+template <class S>
+static long dom_hop_np(const Domains& D, const Box& out, long nlist, int Ls, bool alt) {
+    const long n = nlist > 0 ? nlist : out.Vh;
+    if (alt && !hop_is_small(n, Ls, D.ndom) && hop_is_rows<S>(n, D.pad2.Vh, Ls, D.ndom))
+        return row_grid_x(out, D.ndom);
+    return hop_grid_x(n, Ls, D.ndom, alt);
+}
+
 // Arguments of one block-domain hop (every block in one launch) and its
 // algorithmic bytes.
 template <class S>
@@ -382,7 +400,8 @@ static int dom_hop(mspcg_ctx* c, Field<S> out, const Box& bout, CField<S> in, co
     const HopArgs<S> a = dom_hop_args<S>(c, out, bout, in, bin, out_par, ph, aux, baux, pa,
                                          partials, done, cg, list, nlist, nread, bytes);
     Timed t(c, cg ? MSPCG_KC_HOPDOMCG : MSPCG_KC_HOPDOM, bytes, st);
-    return launch_hop<S>(a, c->Ls, c->dom.ndom, dag, true, st);
+    const HopReach reach = hop_reach(c->dom, list);
+    return launch_hop<S>(a, c->Ls, c->dom.ndom, dag, true, st, &reach);
 }
 
 template <class S>
@@ -485,7 +504,7 @@ struct Local {
     Field<S> rho, p, zz, t, u, y, v;
     InnerScalars sc;
     long hop_np = 0, start_np = 0, upd_np = 0;
-    bool small = true;  // the small-launch hop may be used
+    bool alt = true;  // the small-launch and matrix-core hops may be used
     FiveDProg m14;
 };
 
@@ -508,11 +527,11 @@ static int local_init(mspcg_ctx* c, Local<S>& L) {
         return MSPCG_ENOMEM;
     L.sc = inner_scalars(c);
     if (!L.sc.gam || !L.sc.a || !L.sc.beta || !L.sc.active) return MSPCG_ENOMEM;
-    L.hop_np = hop_grid_x(D.yout(), Ls, D.ndom, L.small);
+    L.hop_np = dom_hop_np<S>(D, D.ybox(), D.yn(), Ls, L.alt);
     const int spb = kThreads / Ls;
     L.start_np = (D.interior.Vh + spb - 1) / spb;
     // partials of the fused update: one per workgroup of the interior hop
-    L.upd_np = hop_grid_x(D.interior.Vh, Ls, D.ndom, L.small);
+    L.upd_np = dom_hop_np<S>(D, D.interior, 0, Ls, L.alt);
     const long vec_np = (nd + kThreads - 1) / kThreads;
     long need = L.hop_np > L.start_np ? L.hop_np : L.start_np;
     if (L.upd_np > need) need = L.upd_np;
@@ -645,7 +664,9 @@ static int precond_core(mspcg_ctx* c, int l, CField<F64> r, Field<F64> z, const 
             const HopArgs<S> a = local_hop<S>(L, k, it, l, done, bytes, dag);
             {
                 Timed t(c, k == 3 ? MSPCG_KC_HOPDOMCG : MSPCG_KC_HOPDOM, bytes, st);
-                if (launch_hop<S>(a, c->Ls, c->dom.ndom, dag, L.small, st)) return MSPCG_EHIP;
+                const HopReach reach = hop_reach(c->dom, a.site_list);
+                if (launch_hop<S>(a, c->Ls, c->dom.ndom, dag, L.alt, st, L.alt ? &reach : nullptr))
+                    return MSPCG_EHIP;
             }
             if (k == 1 && (e = local_alpha<S>(L, done, st))) return e;
         }
@@ -761,7 +782,9 @@ struct BatchPrecondImpl : BatchPrecond {
             double bytes;
             bool dg;
             const HopArgs<S> a = local_hop<S>(L[i], k, it, l, done[i], bytes, dg);
-            if (launch_hop<S>(a, L[i].c->Ls, L[i].c->dom.ndom, dg, L[i].small, st))
+            const HopReach reach = hop_reach(L[i].c->dom, a.site_list);
+            if (launch_hop<S>(a, L[i].c->Ls, L[i].c->dom.ndom, dg, L[i].alt, st,
+                              L[i].alt ? &reach : nullptr))
                 return MSPCG_EHIP;
         }
         return 0;
@@ -803,7 +826,7 @@ static int make_batch_impl(mspcg_ctx* const* cs, int n, int l, const int* const*
     bool all = true;
     for (int i = 0; i < n; ++i) all = all && multi_hop_ls(cs[i]->Ls);
     for (int i = 0; i < n; ++i) {
-        b->L[i].small = !all;
+        b->L[i].alt = !all;
         if ((e = local_init<S>(cs[i], b->L[i]))) return e;
     }
     if (multi && l > 0) {
@@ -829,13 +852,13 @@ size_t precond_partials_need(mspcg_ctx* c) {
     const Domains& D = c->dom;
     const int Ls = c->Ls;
     const long nd = D.interior.Vh * Ls;
-    long hop_np = 0;  // with the small-launch hop and without
-    for (const bool sm : {false, true}) {
-        const long n = hop_grid_x(D.yout(), Ls, D.ndom, sm);
-        if (n > hop_np) hop_np = n;
-    }
-    const long u = hop_grid_x(D.interior.Vh, Ls, D.ndom, true);
-    if (u > hop_np) hop_np = u;
+    long hop_np = 0;  // of every kernel and both reducing hops
+    for (const bool alt : {false, true})
+        for (const long n : {dom_hop_np<F64>(D, D.ybox(), D.yn(), Ls, alt),
+                             dom_hop_np<F16>(D, D.ybox(), D.yn(), Ls, alt),
+                             dom_hop_np<F64>(D, D.interior, 0, Ls, alt),
+                             dom_hop_np<F16>(D, D.interior, 0, Ls, alt)})
+            if (n > hop_np) hop_np = n;
     const int spb = kThreads / Ls;
     const long start_np = (D.interior.Vh + spb - 1) / spb;
     const long vec_np = (nd + kThreads - 1) / kThreads;

@@ -1,5 +1,6 @@
 """Hop launches on both sides of the line between the small-launch kernel and the
-general one (kernels.h, hop_is_small), every compiled Ls, against the FP64 oracle.
+general one (kernels.h, hop_is_small), every compiled Ls, against the FP64 oracle;
+the FP16 matrix-core hop (hop_is_rows) against the FP64 operator.
 
 Bars as in test_gpu_ops.py and test_gpu_mspcg.py: FP64 1e-13, FP32 1e-5, the block
 operator in FP16 storage k16_bars()."""
@@ -9,7 +10,7 @@ import torch
 
 import oracle as O
 from paper_1804_08593_amd import mspcg, synth
-from tests.gpu_util import dev, host, k16_bars, relerr, say, setup, site_err
+from tests.gpu_util import cg16_bars, dev, host, k16_bars, relerr, say, setup, site_err
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +72,26 @@ def test_block_operator_across_launch_sizes(dims, block, Ls, prec):
     bar = {mspcg.FP64: (1e-13, 1e-12), mspcg.FP32: (1e-5, 1e-4), mspcg.FP16: (n16, s16)}[prec]
     say(f"K {dims} {block} Ls={Ls} prec={prec}: {err:.2e} per entry {se:.2e}")
     assert err <= bar[0] and se <= bar[1]
+
+
+@pytest.mark.parametrize("dims,block,pad,c", [
+    ((24, 24, 24, 24), (24, 24, 12, 24), 2, 0.5),  # one cut direction, the others periodic
+    ((20, 28, 18, 32), (10, 14, 6, 16), 2, 0.5),   # odd half extents in every direction
+    ((20, 28, 18, 32), (20, 14, 18, 16), 1, 0.5),  # periodic x and z, pad 1
+    ((16, 24, 28, 32), (8, 12, 14, 16), 0, 0.5),   # no pad
+    ((16, 24, 28, 32), (4, 12, 14, 16), 2, 0.0),   # Shamir, blocks as short as a piece in x
+], ids=lambda v: str(v))
+def test_matrix_core_hop(dims, block, pad, c):
+    Ls, l = 16, 2
+    act, U, ctx = setup(dims, Ls, 1.8, 0.05, 1.0 + c, c, gseed=35)
+    gen = torch.Generator(device="cuda").manual_seed(36)
+    p = torch.randn(ctx.fshape, dtype=torch.complex128, device="cuda", generator=gen)
+    ctx.set_blocking(block, pad)
+    ref, out = torch.zeros_like(p), torch.zeros_like(p)
+    for run, bars in ((lambda o, prec: ctx.apply(mspcg.OP_KBLOCK, p, o, prec=prec), k16_bars()),
+                      (lambda o, prec: ctx.precond(p, o, l, prec=prec), cg16_bars(l))):
+        run(ref, mspcg.FP64)
+        run(out, mspcg.FP16)
+        err, se = relerr(host(out), host(ref)), site_err(host(out), host(ref))
+        say(f"{dims} {block} pad={pad} c={c}: {err:.2e} per entry {se:.2e}")
+        assert err <= bars[0] and se <= bars[1]
