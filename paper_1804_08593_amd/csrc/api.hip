@@ -722,20 +722,14 @@ extern "C" int mspcg_precond(mspcg_ctx* c, int inner_iters, int prec, const void
     MSPCG_HIP(hipSetDevice(c->device));
     int e = domains_setup(c, c->blocking, prec, st);
     if (e) return e;
-    Field<F64> re = half_field<F64>(c, "pc_r", c->Nh);
-    Field<F64> ze = half_field<F64>(c, "pc_z", c->Nh);
-    if (launch_pack_parity<F64>((const double2*)r_dev, re, c->L, c->Ls, 0, st)) return MSPCG_EHIP;
-    int done = 0;
+    const double2* r = (const double2*)r_dev;
+    double2* z = (double2*)z_dev;
     switch (prec) {
-        case MSPCG_FP64: e = precond_apply<F64>(c, inner_iters, cfield(re), ze, st, &done); break;
-        case MSPCG_FP32: e = precond_apply<F32>(c, inner_iters, cfield(re), ze, st, &done); break;
-        case MSPCG_FP16: e = precond_apply<F16>(c, inner_iters, cfield(re), ze, st, &done); break;
+        case MSPCG_FP64: return precond_apply<F64>(c, inner_iters, r, z, st);
+        case MSPCG_FP32: return precond_apply<F32>(c, inner_iters, r, z, st);
+        case MSPCG_FP16: return precond_apply<F16>(c, inner_iters, r, z, st);
         default: return MSPCG_EINVAL;
     }
-    if (e) return e;
-    if (launch_unpack_parity<F64>(cfield(ze), (double2*)z_dev, c->L, c->Ls, 0, 1, st))
-        return MSPCG_EHIP;
-    return MSPCG_OK;
 }
 MSPCG_ABI_CATCH
 

@@ -190,9 +190,9 @@ int ensure_partials(mspcg_ctx* c, size_t n);
 // Domains of the block preconditioner
 int domains_setup(mspcg_ctx* c, const mspcg_blocking& b, int prec, hipStream_t st);
 size_t precond_partials_need(mspcg_ctx* c);
+// z = K_l^-1 r, boundary fields (odd sites of z zero)
 template <class S>
-int precond_apply(mspcg_ctx* c, int inner_iters, CField<F64> r_e, Field<F64> z_e,
-                  hipStream_t st, int* inner_done);
+int precond_apply(mspcg_ctx* c, int inner_iters, const double2* r, double2* z, hipStream_t st);
 // Optional output of precond_apply_flag: with l > 0 the workgroup partials of
 // Re<z, r> and Re<z, q> are left in ctx->partials ([0, np) and [np, 2 np));
 // np stays 0 when they were not formed (l = 0).

@@ -107,6 +107,23 @@ struct DomGeom {
     int L[4], blk[4], nb[4];
 };
 
+// lex index in the lattice of even interior site cb of domain d
+__device__ __forceinline__ long dom_site_lex(const DomGeom& g, int d, long cb, long Vhb) {
+    Box b;
+    for (int m = 0; m < 4; ++m) {
+        b.E[m] = g.blk[m];
+        b.off[m] = 0;
+    }
+    b.Vh = Vhb;
+    int c[4], gc[4];
+    box_coords(b, cb, 0, c);
+    for (int m = 0; m < 4; ++m) {
+        gc[m] = (d % g.nb[m]) * g.blk[m] + c[m];
+        d /= g.nb[m];
+    }
+    return (((long)gc[3] * g.L[2] + gc[2]) * g.L[1] + gc[1]) * g.L[0] + gc[0];
+}
+
 // rho = p = r on the block interior (global FP64 layout -> domain layout),
 // per-domain |rho|^2 partials.
 template <class S>
@@ -120,20 +137,7 @@ __global__ void inner_start_kernel(CField<F64> r, Field<S> rho, Field<S> p, DomG
     const bool active = (int)threadIdx.x < spb * Ls && cb < Vhb;
     double n2 = 0;
     if (active) {
-        Box b;
-        for (int m = 0; m < 4; ++m) {
-            b.E[m] = g.blk[m];
-            b.off[m] = 0;
-        }
-        b.Vh = Vhb;
-        int c[4];
-        box_coords(b, cb, 0, c);
-        int rr = d, gc[4];
-        for (int m = 0; m < 4; ++m) {
-            gc[m] = (rr % g.nb[m]) * g.blk[m] + c[m];
-            rr /= g.nb[m];
-        }
-        const long gcb = ((((long)gc[3] * g.L[2] + gc[2]) * g.L[1] + gc[1]) * g.L[0] + gc[0]) >> 1;
+        const long gcb = dom_site_lex(g, d, cb, Vhb) >> 1;
         cx<double> v[12];
         load_spinor_at<F64>(r, gcb * Ls, s, Ls, v);
         cx<typename S::real> w[12];
@@ -147,6 +151,65 @@ __global__ void inner_start_kernel(CField<F64> r, Field<S> rho, Field<S> p, DomG
         store_spinor_at<S>(p, ib, s, Ls, w);
     }
     block_reduce_store(n2, partials + (long)d * gridDim.x + blockIdx.x);
+}
+
+// The same from a boundary field.  Bound by HBM; with the internal FP64 copy of r
+// in between (two passes) 24^3x48x16 in FP16 took 405 + 333 us, now 321.
+template <class S, int LS>
+__global__ __launch_bounds__(256) void start_full_kernel(const double2* r, Field<S> rho,
+                                                         Field<S> p, DomGeom g, long V4, long Vhb,
+                                                         double* partials) {
+    using T = typename S::real;
+    constexpr int SPB = 256 / LS;
+    __shared__ __attribute__((aligned(16))) cx<T> lds[SPB * 12 * (LS + 1)];
+    __shared__ int lexs[SPB];
+    const int sl = threadIdx.x / LS, s = threadIdx.x - sl * LS, d = blockIdx.y;
+    const long first = (long)blockIdx.x * SPB;
+    if ((int)threadIdx.x < SPB) {
+        const long cb = first + threadIdx.x;
+        lexs[threadIdx.x] = cb < Vhb ? (int)dom_site_lex(g, d, cb, Vhb) : -1;
+    }
+    __syncthreads();
+    load_boundary<T, LS>(lds, lexs, r, V4);
+    __syncthreads();
+    double n2 = 0;
+    if (sl < SPB && first + sl < Vhb) {
+        cx<T> w[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            w[c] = lds[(sl * 12 + c) * (LS + 1) + s];
+            n2 += (double)w[c].re * w[c].re + (double)w[c].im * w[c].im;
+        }
+        const long ib = ((long)d * Vhb + first + sl) * LS;
+        store_spinor_at<S>(rho, ib, s, LS, w);
+        store_spinor_at<S>(p, ib, s, LS, w);
+    }
+    block_reduce_store(n2, partials + (long)d * gridDim.x + blockIdx.x);
+}
+
+// z on the blocks (domain layout) -> boundary field, odd sites zero.  With an
+// internal FP64 copy in between 24^3x48x16 in FP16 took 235 + 589 us, now 488.
+template <class S, int LS>
+__global__ __launch_bounds__(256) void finish_full_kernel(CField<S> z, double2* full, DomGeom g,
+                                                          long V4, long Vhb) {
+    using T = typename S::real;
+    constexpr int SPB = 256 / LS;
+    __shared__ __attribute__((aligned(16))) cx<T> lds[SPB * 12 * (LS + 1)];
+    __shared__ int lexs[SPB];
+    const int sl = threadIdx.x / LS, s = threadIdx.x - sl * LS, d = blockIdx.y;
+    const long first = (long)blockIdx.x * SPB;
+    if ((int)threadIdx.x < SPB) {
+        const long cb = first + threadIdx.x;
+        lexs[threadIdx.x] = cb < Vhb ? (int)dom_site_lex(g, d, cb, Vhb) : -1;
+    }
+    if (sl < SPB && first + sl < Vhb) {
+        cx<T> v[12];
+        load_spinor_at<S, true>(z, ((long)d * Vhb + first + sl) * LS, s, LS, v);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) lds[(sl * 12 + c) * (LS + 1) + s] = v[c];
+    }
+    __syncthreads();
+    store_boundary<T, LS>(lds, lexs, full, V4, 1, (int)blockDim.x);
 }
 
 int last_error() { return hipGetLastError() == hipSuccess ? 0 : MSPCG_EHIP; }
@@ -544,23 +607,44 @@ static int local_init(mspcg_ctx* c, Local<S>& L) {
     return 0;
 }
 
-// rho = p = r on every block, gamma = |rho|^2 per block
+static DomGeom dom_geom(const mspcg_ctx* c) {
+    DomGeom g;
+    for (int m = 0; m < 4; ++m) {
+        g.L[m] = c->L[m];
+        g.blk[m] = c->dom.blk[m];
+        g.nb[m] = c->dom.nb[m];
+    }
+    return g;
+}
+
+// rho = p = r on every block, gamma = |rho|^2 per block; r: an internal FP64 field,
+// or a boundary field if `full` is given
 template <class S>
-static int local_start(Local<S>& L, CField<F64> r, const int* done, hipStream_t st) {
+static int local_start(Local<S>& L, CField<F64> r, const double2* full, const int* done,
+                       hipStream_t st) {
     mspcg_ctx* c = L.c;
     const Domains& D = c->dom;
     const int Ls = c->Ls;
     const long nd = D.interior.Vh * Ls;
-    DomGeom g;
-    for (int m = 0; m < 4; ++m) {
-        g.L[m] = c->L[m];
-        g.blk[m] = D.blk[m];
-        g.nb[m] = D.nb[m];
-    }
+    const DomGeom g = dom_geom(c);
     const int spb = kThreads / Ls;
     Timed t(c, MSPCG_KC_BLAS, (double)D.ndom * nd * (192.0 + 2 * S::bytes_spinor), st);
-    hipLaunchKernelGGL(inner_start_kernel<S>, dim3((unsigned)L.start_np, D.ndom), dim3(spb * Ls), 0,
-                       st, r, L.rho, L.p, g, Ls, D.interior.Vh, c->partials, done);
+    const dim3 grid((unsigned)L.start_np, D.ndom);
+    if (full) {
+        switch (Ls) {
+#define MSPCG_CASE(N)                                                                            \
+    case N:                                                                                      \
+        hipLaunchKernelGGL((start_full_kernel<S, N>), grid, dim3(256), 0, st, full, L.rho, L.p, g, \
+                           c->V4, D.interior.Vh, c->partials);                                   \
+        break;
+            MSPCG_LS_LIST(MSPCG_CASE)
+#undef MSPCG_CASE
+            default: return MSPCG_EINVAL;
+        }
+    } else {
+        hipLaunchKernelGGL(inner_start_kernel<S>, grid, dim3(spb * Ls), 0, st, r, L.rho, L.p, g,
+                           Ls, D.interior.Vh, c->partials, done);
+    }
     if (last_error()) return MSPCG_EHIP;
     hipLaunchKernelGGL(inner_start_scalars, dim3(D.ndom), dim3(kThreads), 0, st, L.sc, c->partials,
                        (int)L.start_np, done);
@@ -647,15 +731,38 @@ static int local_finish(Local<S>& L, int l, Field<F64> z, PrecondDots* dots, hip
     return 0;
 }
 
+// z written to a boundary field, odd sites zero
+template <class S>
+static int local_finish_full(Local<S>& L, int l, double2* full, hipStream_t st) {
+    mspcg_ctx* c = L.c;
+    const Domains& D = c->dom;
+    Timed t(c, MSPCG_KC_BLAS, (double)c->Nh * (2 * 192.0 + S::bytes_spinor), st);
+    if (l == 0) return launch_zero(full, 2 * c->Nh, st) ? MSPCG_EHIP : 0;
+    const dim3 grid((unsigned)L.start_np, D.ndom);
+    switch (c->Ls) {
+#define MSPCG_CASE(N)                                                                             \
+    case N:                                                                                       \
+        hipLaunchKernelGGL((finish_full_kernel<S, N>), grid, dim3(256), 0, st, cfield(L.zz), full, \
+                           dom_geom(c), c->V4, D.interior.Vh);                                    \
+        break;
+        MSPCG_LS_LIST(MSPCG_CASE)
+#undef MSPCG_CASE
+        default: return MSPCG_EINVAL;
+    }
+    return last_error();
+}
+
 // z_e = K_l^-1 r_e (FP64 whole-lattice even fields); `done` (device flag,
-// may be null) skips the work once the outer solve has converged.
+// may be null) skips the work once the outer solve has converged.  full_r, full_z:
+// boundary fields in their place.
 template <class S>
 static int precond_core(mspcg_ctx* c, int l, CField<F64> r, Field<F64> z, const int* done,
-                        hipStream_t st, PrecondDots* dots = nullptr) {
+                        hipStream_t st, PrecondDots* dots = nullptr,
+                        const double2* full_r = nullptr, double2* full_z = nullptr) {
     Local<S> L;
     int e;
     if ((e = local_init<S>(c, L))) return e;
-    if ((e = local_start<S>(L, r, done, st))) return e;
+    if ((e = local_start<S>(L, r, full_r, done, st))) return e;
     for (int it = 0; it < l; ++it) {
         if ((e = local_B<S>(L, it, done, st))) return e;
         for (int k = 0; k < 4; ++k) {
@@ -672,6 +779,7 @@ static int precond_core(mspcg_ctx* c, int l, CField<F64> r, Field<F64> z, const 
         }
         if (it + 1 < l && (e = local_beta<S>(L, done, st))) return e;
     }
+    if (full_z) return local_finish_full<S>(L, l, full_z, st);
     return local_finish<S>(L, l, z, dots, st);
 }
 
@@ -794,7 +902,7 @@ struct BatchPrecondImpl : BatchPrecond {
         const size_t n = L.size();
         int e;
         for (size_t i = 0; i < n; ++i)
-            if ((e = local_start<S>(L[i], r[i], done[i], st))) return e;
+            if ((e = local_start<S>(L[i], r[i], nullptr, done[i], st))) return e;
         for (int it = 0; it < l; ++it) {
             for (size_t i = 0; i < n; ++i)
                 if ((e = local_B<S>(L[i], it, done[i], st))) return e;
@@ -868,8 +976,8 @@ size_t precond_partials_need(mspcg_ctx* c) {
 }
 
 template <class S>
-int precond_apply(mspcg_ctx* c, int l, CField<F64> r, Field<F64> z, hipStream_t st, int*) {
-    return precond_core<S>(c, l, r, z, nullptr, st);
+int precond_apply(mspcg_ctx* c, int l, const double2* r, double2* z, hipStream_t st) {
+    return precond_core<S>(c, l, CField<F64>{}, Field<F64>{}, nullptr, st, nullptr, r, z);
 }
 
 template <class S>
@@ -900,8 +1008,7 @@ template int block_A<F32>(mspcg_ctx*, Field<F32>, CField<F32>, double*, const in
 template int block_A<F16>(mspcg_ctx*, Field<F16>, CField<F16>, double*, const int*, hipStream_t);
 
 #define MSPCG_PC(S)                                                                         \
-    template int precond_apply<S>(mspcg_ctx*, int, CField<F64>, Field<F64>, hipStream_t,   \
-                                  int*);                                                    \
+    template int precond_apply<S>(mspcg_ctx*, int, const double2*, double2*, hipStream_t);  \
     template int precond_apply_flag<S>(mspcg_ctx*, int, CField<F64>, Field<F64>,           \
                                        const int*, hipStream_t, PrecondDots*);              \
     template int kblock_apply<S>(mspcg_ctx*, CField<F64>, Field<F64>, hipStream_t);

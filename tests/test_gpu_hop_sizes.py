@@ -95,3 +95,26 @@ def test_matrix_core_hop(dims, block, pad, c):
         err, se = relerr(host(out), host(ref)), site_err(host(out), host(ref))
         say(f"{dims} {block} pad={pad} c={c}: {err:.2e} per entry {se:.2e}")
         assert err <= bars[0] and se <= bars[1]
+
+
+@pytest.mark.parametrize("prec", [mspcg.FP64, mspcg.FP32, mspcg.FP16])
+@pytest.mark.parametrize("dims,block,Ls", [
+    ((6, 4, 6, 4), (2, 4, 2, 4), 2),     # a workgroup holds more sites than a block
+    ((8, 6, 6, 4), (4, 2, 6, 4), 6),     # 60 of 64 lanes, a ragged last workgroup
+    ((6, 8, 4, 8), (6, 4, 4, 2), 20),
+    ((4, 6, 8, 4), (4, 6, 4, 4), 32),
+], ids=lambda v: str(v))
+def test_preconditioner_fields_in_and_out(dims, block, Ls, prec):
+    act, U, ctx = setup(dims, Ls, 1.8, 0.05, 1.5, 0.5, gseed=37)
+    r = synth.fermion_field(dims, Ls, 38)  # odd sites are ignored
+    ctx.set_blocking(block, 2)
+    z = torch.full_like(dev(r), 7.0)
+    for l in (0, 1):
+        ctx.precond(dev(r), z, l, prec=prec)
+        got = host(z)
+        assert np.all(O.parity_mask(act, got, 1) == 0)
+        ref = O.inner_block_cg(act, U, O.parity_mask(act, r, 0), block, l, "literal")
+        bar = {mspcg.FP64: (1e-12, 1e-11), mspcg.FP32: (1e-5, 1e-4), mspcg.FP16: cg16_bars(l)}[prec]
+        err, se = relerr(got, ref), site_err(got, ref)
+        say(f"precond {dims} {block} Ls={Ls} prec={prec} l={l}: {err:.2e} per entry {se:.2e}")
+        assert err <= bar[0] and se <= bar[1]
