@@ -139,7 +139,11 @@ __device__ __forceinline__ double strided_sum(const double* p, int n) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) v += t[k];
     }
-    for (; i < n; i += B) v += p[i];
+    double t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = i + k * B < n ? p[i + k * B] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v += t[k];
     return v;
 }
 

@@ -88,6 +88,25 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
             xd = load_comp<S>(a.aux, ab, s, LS, 6 + wv);
         }
     }
+    // and what the fused update reads of them: loaded where it is used, each load
+    // waited behind the store before it (8^4x8 in FP64 12.2 -> 11.1 us, in FP32 9.1 -> 7.8)
+    cx<T> cr[2], cp[2], cxv[2];
+    T al = 0;
+    if constexpr (CG && !S::has_scale) {
+        al = (T)(a.cg_alpha ? a.cg_alpha[d] : a.cg_sc->alpha);
+        if (wv < 6 && active) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int q = wv + 6 * h;
+                cr[h] = load_comp<S>(cfield(a.cg_r), obase, s, LS, q);
+                cp[h] = cxv[h] = {0, 0};
+                if (a.cg_x.data) {
+                    cp[h] = load_comp<S>(a.cg_p, obase, s, LS, q);
+                    if (!a.cg_first) cxv[h] = load_comp<S>(cfield(a.cg_x), obase, s, LS, q);
+                }
+            }
+        }
+    }
 
     // direction wv: w = U (psi_up + sig e psi_dn) of the neighbour
     constexpr int SF = DAG ? 1 : -1;
@@ -274,23 +293,21 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
         };
         if constexpr (CG) {
             // r -= alpha out, x += alpha p
-            const T al = (T)(a.cg_alpha ? a.cg_alpha[d] : a.cg_sc->alpha);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int q = c + 6 * h;
                 const cx<T> o = h ? rd : ru;
-                cx<T> v = load_comp<S>(cfield(a.cg_r), obase, s, LS, q);
+                cx<T> v = cr[h];
                 v.re -= al * o.re;
                 v.im -= al * o.im;
                 square(v);
                 store_comp<S>(a.cg_r, obase, s, LS, q, v);
                 if (a.cg_x.data) {
-                    const cx<T> p = load_comp<S>(a.cg_p, obase, s, LS, q);
-                    cx<T> x = {al * p.re, al * p.im};
+                    cx<T> x = {al * cp[h].re, al * cp[h].im};
                     if (!a.cg_first) {
-                        x = load_comp<S>(cfield(a.cg_x), obase, s, LS, q);
-                        x.re += al * p.re;
-                        x.im += al * p.im;
+                        x = cxv[h];
+                        x.re += al * cp[h].re;
+                        x.im += al * cp[h].im;
                     }
                     store_comp<S>(a.cg_x, obase, s, LS, q, x);
                 }

