@@ -476,12 +476,13 @@ extern "C" int mspcg_create(const mspcg_action* a, int device, mspcg_ctx** out) 
     c->evused = 0;
     // measured defaults: 4D tiles of whole x rows help the FP64/FP32 whole-lattice
     // hop, the lexicographic order is best for the FP16 block hops.  Mhat^+ with
-    // rows x 8^3 against 8x4^3, FP64 / FP32 us: 16^3x32x12 347 / 216 against 369 /
-    // 226, 24^3x48x16 2142 / 1371 against 2212 / 1432, 16^4x12 191 / 116 against 203 /
-    // 118, 32^4x12 2777 / 1702 against 2795 / 1726, 18x14x20x26x10 328 / 196 against
-    // 338 / 200
+    // rows x 4x8x16 against rows x 8^3 against 8^3 x 16, FP64 / FP32 us: 16^3x32x12 349 /
+    // 217, 347 / 217, 356 / 221; 24^3x48x16 2138 / 1378, 2151 / 1375, 2159 / 1401; 16^4x12
+    // 192 / 115, 192 / 117, 194 / 116; 32^4x12 2737 / 1683, 2787 / 1709, 2786 / 1737;
+    // 18x14x20x26x10 331 / 198, 331 / 197, 340 / 200; the four hops of a CG step on
+    // 24^3x48x16 3847, 3876, 3858
     c->tune.xcd_remap = 1;
-    const int t64[4] = {1 << 16, 8, 8, 8};
+    const int t64[4] = {1 << 16, 4, 8, 16};
     for (int m = 0; m < 4; ++m) {
         c->tune.tile[MSPCG_FP64][m] = t64[m];
         c->tune.tile[MSPCG_FP32][m] = t64[m];

@@ -30,10 +30,10 @@
 // descriptor of length zero, which returns zeros without touching memory.
 //
 // 24^3 x 48 x 16 in 16 blocks, the four hops of the block operator, against the
-// general kernel: u 327 (373), y 456 (524), v 333 (400), w 304 (325) us.  The w hop
-// moves 3.9 TB/s (copy 4.7); the u hop has its vector unit busy for two thirds of
-// the time (233 instructions an output, 96 of them the scaled sums); the other
-// hops lie between.  More waves than 3 a SIMD need registers that
+// general kernel: u 327 (373), y 456 (524), v 333 (400), w 304 (325) us.  v and w are
+// bound by what passes between L2 and memory, 6.1 TB/s; u by its vector
+// instructions, issued two thirds of the time (233 an output, 96 of them the
+// scaled sums); y lies between.  More waves than 3 a SIMD need registers that
 // spill (u 393 us at 4).
 // The 5D programs move values along s with DPP row shifts instead of LDS.
 //
