@@ -50,8 +50,9 @@ DEFAULT = "dwf_moebius_24c48_ls16"
 # committed rocprofv3 counter summaries (HBM bytes per launch of a kernel
 # class), valid only for the kernel sources they were taken on
 KERNEL_SOURCES = {
-    "hop64": ["hop_impl.h", "hop_f64.hip", "common.h", "fived.h", "api.hip"],
-    "hopdom": ["hop_impl.h", "hop_f16.hip", "common.h", "fived.h", "precond.hip"],
+    "hop64": ["hop_impl.h", "hop_f64.hip", "hop_f64_wide.hip", "common.h", "fived.h", "api.hip"],
+    "hopdom": ["hop_impl.h", "hop_rows.h", "hop_f16.hip", "hop_f16_wide.hip", "hop_f16_rows.hip",
+               "common.h", "kernels.h", "fived.h", "precond.hip"],
 }
 
 
