@@ -29,12 +29,14 @@
 // whole wave and runs on the scalar unit; a dropped hop reads through a buffer
 // descriptor of length zero, which returns zeros without touching memory.
 //
-// 24^3 x 48 x 16 in 16 blocks, the four hops of the block operator, against the
-// general kernel: u 327 (373), y 456 (524), v 333 (400), w 304 (325) us.  v and w are
-// bound by what passes between L2 and memory, 6.1 TB/s; u by its vector
-// instructions, issued two thirds of the time (233 an output, 96 of them the
-// scaled sums); y lies between.  More waves than 3 a SIMD need registers that
-// spill (u 393 us at 4).
+// 24^3 x 48 x 16 in 16 blocks, hops u / y / v of the block operator: 329 / 460 / 335 us
+// (general kernel 373 / 524 / 400).  v is bound by what passes between L2 and
+// memory, 6.1 TB/s; u by its vector instructions, issued two thirds of the time
+// (233 an output, 96 of them the scaled sums); y lies between.  More waves than 3
+// a SIMD need registers that spill (u 393 us at 4).  The hop with the fused
+// update stays with the general kernel: here it took 306 us, 489 with the update
+// of x (there 326 on average), and left the 5D kernel behind it less in cache (277
+// against 250 us).
 // The 5D programs move values along s with DPP row shifts instead of LDS.
 //
 #pragma once
@@ -283,10 +285,9 @@ __device__ __forceinline__ void row_store(const RowField& f, int site, bool ok, 
 // (bx+1)*kRowWaves) of domain d, one per wave.  A piece is `chunk` steps of x of
 // one strip; the pieces of a strip follow each other, so that the slices of inputs
 // that two of them load are found in L2.
-// CG: 1 subtracts alpha out from cg_r, 2 updates cg_x as well.
 // INV: the hop's program holds an inverse step, and there is neither aux nor
 // partials; else no inverse step.
-template <bool DAG, bool INV, int CG>
+template <bool DAG, bool INV>
 __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int gx) {
     const int lane = (int)(threadIdx.x & 63), grp = lane >> 4, s = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -323,7 +324,6 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
     unsigned far = 0;
     RowBidi kh, ka;
     RowInv ki;
-    float al = 0.f;
     RowField in, out, aux;
     const char* linkp;
     RowProg ph, pa;
@@ -399,10 +399,7 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
         in.set(a.in, d, g.in.Vh);
         in_x = g.out.off[0] - g.in.off[0];
         in_E = g.periodic & 1 ? -g.in.E[0] : g.in.E[0];
-        if constexpr (CG)
-            out.set(a.cg_r, d, g.out.Vh);
-        else
-            out.set(a.out, d, g.out.Vh);
+        out.set(a.out, d, g.out.Vh);
         linkp = reinterpret_cast<const char*>(a.links + (long)d * a.link_dom_stride +
                                               (long)g.out_par * g.link.Vh * 72);
         link_x = g.out.off[0] - g.link.off[0];
@@ -428,7 +425,6 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
             pa = a.ra;
             ka.set(a.ra, s);
         }
-        if constexpr (CG) al = (float)(a.cg_alpha ? a.cg_alpha[d] : a.cg_sc->alpha);
     }
     double n2 = 0;
 
@@ -481,29 +477,16 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
     // what an output reads at its own site.  Issued before the loads for the next
     // output, so that the wait for them leaves those in flight.
     struct Own {
-        RowSite ya, yr, yp, yx;
+        RowSite ya;
     };
     auto issue_own = [&](auto cc, int x, bool want, Own& o) {
         constexpr int C = decltype(cc)::value;
-        const int oat = __builtin_amdgcn_readlane(rows, 32 + C) + (x >> 1);
         // aux lives on its own box; sites outside it contribute zero
         if constexpr (!INV)
             o.ya = row_load<2>(
                 aux, __builtin_amdgcn_readlane(rows, 48 + C) + ((x + aux_x) >> 1),
                 want && ((valid_aux >> C) & 1) && (unsigned)(x + aux_x) < (unsigned)aux_E,
                 lane_off, sc_ld);
-        if constexpr (CG) {
-            o.yr = row_load<2>(out, oat, want, lane_off, sc_ld);
-        }
-        if constexpr (CG == 2) {
-            const RowArgs& a = row_args(ap);
-            RowField fp, fx;
-            fp.set(a.cg_p, d, a.g.out.Vh);
-            fx.set(a.cg_x, d, a.g.out.Vh);
-            o.yp = row_load<2>(fp, oat, want, lane_off, sc_ld);
-            if (a.cg_first) fx.sites = 0;
-            o.yx = row_load<2>(fx, oat, want, lane_off, sc_ld);
-        }
     };
     // the output at corner C and x; hk: the scales of b.h; xm, xp: the inputs at
     // x - 1 and x + 1, own: those at x
@@ -515,7 +498,7 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
                       const RowSite (&xp)[4]) {
         constexpr int C = decltype(cc)::value;
         using std::integral_constant;
-        RowSite so{nt_u4{0, 0, 0, 0}, 0.f}, sx{nt_u4{0, 0, 0, 0}, 0.f};
+        RowSite so{nt_u4{0, 0, 0, 0}, 0.f};
         if (want) {
             RowHalf v;
 #pragma unroll
@@ -601,50 +584,19 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
                     v.d[c] += y.d[c];
                 }
             }
-            float t2 = 0;
-            if constexpr (CG) {
-                // fused CG update: r -= alpha out, x += alpha p, partials of |r|^2
-                RowHalf r;
-                row_decode(o.yr, r);
+            so = row_encode(v);
+            if constexpr (!INV) {
+                float t2 = 0;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    r.u[c] -= al * v.u[c];
-                    t2 = fmadd(r.u[c], r.u[c], t2);
-                    r.d[c] -= al * v.d[c];
-                    t2 = fmadd(r.d[c], r.d[c], t2);
+                    t2 = fmadd(v.u[c], v.u[c], t2);
+                    t2 = fmadd(v.d[c], v.d[c], t2);
                 }
-                so = row_encode(r);
-                if constexpr (CG == 2) {
-                    RowHalf p, z;
-                    row_decode(o.yp, p);
-                    row_decode(o.yx, z);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        z.u[c] += al * p.u[c];
-                        z.d[c] += al * p.d[c];
-                    }
-                    sx = row_encode(z);
-                }
-            } else {
-                so = row_encode(v);
-                if constexpr (!INV) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        t2 = fmadd(v.u[c], v.u[c], t2);
-                        t2 = fmadd(v.d[c], v.d[c], t2);
-                    }
-                }
+                n2 += (double)t2;
             }
-            if constexpr (!INV) n2 += (double)t2;
         }
         const int oat = __builtin_amdgcn_readlane(rows, 32 + C) + (x >> 1);
-        row_store<CG ? 0 : 2>(out, oat, want, lane_off, sc_ld, so);
-        if constexpr (CG == 2) {
-            const RowArgs& a = row_args(ap);
-            RowField fx;
-            fx.set(a.cg_x, d, a.g.out.Vh);
-            row_store<0>(fx, oat, want, lane_off, sc_ld, sx);
-        }
+        row_store<2>(out, oat, want, lane_off, sc_ld, so);
     };
 
     if (xlo < xhi) {
@@ -723,7 +675,7 @@ __device__ __forceinline__ void row_body(const RowArgs* ap, int bx, int d, int g
     }
     if constexpr (!INV) {
         const RowArgs& a = row_args(ap);
-        if (CG || a.partials) block_sum_store<F16, LS>(n2, a.partials + (long)d * gx + bx);
+        if (a.partials) block_sum_store<F16, LS>(n2, a.partials + (long)d * gx + bx);
     }
 }
 

@@ -111,17 +111,15 @@ struct HopReach {
 
 // Arguments of the FP16 matrix-core hop (hop_rows.h), from HopArgs.
 struct RowArgs {
-    CField<F16> in, aux, cg_p;
-    Field<F16> out, cg_r, cg_x;
+    CField<F16> in, aux;
+    Field<F16> out;
     const __half2* links;
     long link_dom_stride;
     HopGeom g;
     RowProg rh, ra;
-    int has_aux, chunk, reach, blk[4], xcd_remap, cg_first;
+    int has_aux, chunk, reach, blk[4], xcd_remap;
     double* partials;
     const int* done;
-    const DevScalars* cg_sc;
-    const double* cg_alpha;
 };
 
 // x extent of a strip piece of the FP16 matrix-core hop.  A piece loads two
@@ -179,7 +177,7 @@ long hop_grid_x(long Vh, int Ls, int ndom, bool small);
 inline bool hop_is_small(long Vh, int Ls, int ndom) { return Vh * Ls * ndom <= 42000; }
 
 // Whether an FP16 block hop onto Vh sites of each of ndom domains takes the
-// matrix-core kernel, and its workgroups per domain.  Ls = 16 fills the columns
+// matrix-core kernel (never one with the fused update, see there), and its workgroups per domain.  Ls = 16 fills the columns
 // of its matrix instruction (with Ls = 12 in them, 24^4 in 12^4 blocks, six local
 // steps took 6138 us against the general kernel's 5657).  It needs enough sites
 // for strips of some length on every wave slot: 16^3 x 32 (65536 sites) in 8^3 x 16

@@ -393,7 +393,7 @@ static HopReach hop_reach(const Domains& D, const int* list) {
 }
 
 // workgroups per domain of a block hop onto box `out` (nlist > 0: onto nlist of
-// its sites); alt: the small-launch and matrix-core kernels may be used
+// its sites, no fused update); alt: the small-launch and matrix-core kernels may be used
 template <class S>
 static long dom_hop_np(const Domains& D, const Box& out, long nlist, int Ls, bool alt) {
     const long n = nlist > 0 ? nlist : out.Vh;
@@ -597,7 +597,7 @@ static int local_init(mspcg_ctx* c, Local<S>& L) {
     const int spb = kThreads / Ls;
     L.start_np = (D.interior.Vh + spb - 1) / spb;
     // partials of the fused update: one per workgroup of the interior hop
-    L.upd_np = dom_hop_np<S>(D, D.interior, 0, Ls, L.alt);
+    L.upd_np = hop_grid_x(D.interior.Vh, Ls, D.ndom, L.alt);
     const long vec_np = (nd + kThreads - 1) / kThreads;
     long need = L.hop_np > L.start_np ? L.hop_np : L.start_np;
     if (L.upd_np > need) need = L.upd_np;
@@ -967,8 +967,7 @@ size_t precond_partials_need(mspcg_ctx* c) {
     for (const bool alt : {false, true})
         for (const long n : {dom_hop_np<F64>(D, D.ybox(), D.yn(), Ls, alt),
                              dom_hop_np<F16>(D, D.ybox(), D.yn(), Ls, alt),
-                             dom_hop_np<F64>(D, D.interior, 0, Ls, alt),
-                             dom_hop_np<F16>(D, D.interior, 0, Ls, alt)})
+                             hop_grid_x(D.interior.Vh, Ls, D.ndom, alt)})
             if (n > hop_np) hop_np = n;
     const int spb = kThreads / Ls;
     const long start_np = (D.interior.Vh + spb - 1) / spb;
