@@ -573,7 +573,20 @@ static int apply_prec(mspcg_ctx* c, int op, const double2* in, double2* out, hip
         if ((e = (x)) != 0) return e < 0 ? MSPCG_EHIP : e; \
     } while (0)
     if (op == MSPCG_OP_M5INV) {
-        T_(launch_prog_full<S>(in, out, P.M5inv, c->act.mf, c->L, c->Ls, st));
+        // one pass, unless the two ranges overlap: its workgroups write sites that
+        // others have yet to read, where every other operator has read all of `in`
+        // before its last hop
+        const long n = 24 * c->Nh;
+        if (in + n <= out || out + n <= in) {
+            T_(launch_prog_full<S>(in, out, P.M5inv, c->act.mf, c->L, c->Ls, st));
+            return MSPCG_OK;
+        }
+        const Field<S> t[2] = {half_field<S>(c, pfx + "ap_te", c->Nh),
+                               half_field<S>(c, pfx + "ap_to", c->Nh)};
+        if (!t[0].data || !t[1].data) return MSPCG_ENOMEM;
+        T_(launch_pack_prog<S>(in, nullptr, t, P.M5inv, c->act.mf, c->L, c->Ls, 0, 2, st));
+        for (int par = 0; par < 2; ++par)
+            T_(launch_unpack_parity<S>(cfield(t[par]), out, c->L, c->Ls, par, 0, st));
         return MSPCG_OK;
     }
     // full operators read and write both parities, the others even fields

@@ -140,3 +140,25 @@ def test_binding_rejects_fields_of_the_wrong_size():
         mspcg.solve_batch([ctx], [t, t], [torch.zeros_like(t)], mspcg.make_params())
     # a field of the right size still goes through (a flat view included)
     ctx.apply(mspcg.OP_D, t.reshape(-1), torch.zeros_like(t))
+
+
+@pytest.mark.parametrize("prec", [mspcg.FP64, mspcg.FP32])
+@pytest.mark.parametrize("dims,Ls", [((4, 4, 2, 6), 12), ((12, 12, 12, 14), 4)],
+                         ids=lambda v: str(v))
+def test_overlapping_input_and_output(dims, Ls, prec):
+    """Input and output that share a part of one buffer (either order, offsets of a few
+    sites, of an s slice and of most of the field): the same bits as apart."""
+    act, U, ctx = setup(dims, Ls, 1.8, 0.05, 1.5, 0.5, gseed=41)
+    psi = dev(synth.fermion_field(dims, Ls, 42)).reshape(-1)
+    n = psi.numel()
+    for op in OPS:
+        ref = torch.empty_like(psi)
+        ctx.apply(op, psi, ref, prec=prec)
+        for k in (12, 12 * 7, n // Ls, n - 12):
+            for first in (0, 1):  # the output lies before, behind the input
+                buf = torch.zeros(n + k, dtype=psi.dtype, device="cuda")
+                inp, out = (buf[k:], buf[:n]) if first == 0 else (buf[:n], buf[k:])
+                inp.copy_(psi)
+                say(f"op={op} prec={prec} offset {k} order {first}")
+                ctx.apply(op, inp, out, prec=prec)
+                assert torch.equal(out, ref)
