@@ -88,25 +88,6 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
             xd = load_comp<S>(a.aux, ab, s, LS, 6 + wv);
         }
     }
-    // and what the fused update reads of them: loaded where it is used, each load
-    // waited behind the store before it (8^4x8 in FP64 12.2 -> 11.1 us, in FP32 9.1 -> 7.8)
-    cx<T> cr[2], cp[2], cxv[2];
-    T al = 0;
-    if constexpr (CG && !S::has_scale) {
-        al = (T)(a.cg_alpha ? a.cg_alpha[d] : a.cg_sc->alpha);
-        if (wv < 6 && active) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int q = wv + 6 * h;
-                cr[h] = load_comp<S>(cfield(a.cg_r), obase, s, LS, q);
-                cp[h] = cxv[h] = {0, 0};
-                if (a.cg_x.data) {
-                    cp[h] = load_comp<S>(a.cg_p, obase, s, LS, q);
-                    if (!a.cg_first) cxv[h] = load_comp<S>(cfield(a.cg_x), obase, s, LS, q);
-                }
-            }
-        }
-    }
 
     // direction wv: w = U (psi_up + sig e psi_dn) of the neighbour
     constexpr int SF = DAG ? 1 : -1;
@@ -153,6 +134,34 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
         for (int c = 0; c < 6; ++c) lds[(D * 6 + c) * 64 + e] = w[c];
         if constexpr (S::has_scale) lk[D * 64 + e] = k;
     });
+    // What the fused update reads of components c and 6 + c of wave c < 6, all before
+    // the first store: a load behind a store waits for a latency of its own.  Ahead of
+    // the products its registers came on top of theirs (FP64 at Ls = 6 .. 16 130-132
+    // VGPRs against 104-116, one workgroup a CU instead of two: Ls = 8, 512 workgroups
+    // 15.9 us against 12.5; 256 workgroups 9.9 and 10.3).  LATE: behind the 5D programs,
+    // where their vectors along s would cost a workgroup of a CU again (FP64 Ls = 16, 512
+    // workgroups 17.3 -> 13.3 us; FP32 Ls = 20, 640 workgroups 14.8 -> 11.0).
+    constexpr bool LATE = sizeof(T) == 8 ? LS == 16 || LS == 20 : LS == 20 || LS == 24;
+    cx<T> cr[2], cp[2], cxv[2];
+    T al = 0;
+    auto operands = [&]() {
+        if constexpr (CG && !S::has_scale) {
+            al = (T)(a.cg_alpha ? a.cg_alpha[d] : a.cg_sc->alpha);
+            if (wv < 6 && active) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int q = wv + 6 * h;
+                    cr[h] = load_comp<S>(cfield(a.cg_r), obase, s, LS, q);
+                    cp[h] = cxv[h] = {0, 0};
+                    if (a.cg_x.data) {
+                        cp[h] = load_comp<S>(a.cg_p, obase, s, LS, q);
+                        if (!a.cg_first) cxv[h] = load_comp<S>(cfield(a.cg_x), obase, s, LS, q);
+                    }
+                }
+            }
+        }
+    };
+    if constexpr (!LATE) operands();
     __syncthreads();
 
     // wave c = 3 sp + colour < 6: the sums of components c and 6 + c (reconstruct)
@@ -219,6 +228,7 @@ __global__ __launch_bounds__(kSmallThreads) void hop_small_kernel(HopArgs<S> a) 
             if (xp) xu = lx[c * 64 + e], xd = lx[(6 + c) * 64 + e];
         }
     }
+    if constexpr (LATE) operands();
     if (a.ph.identity) {
         ru.re *= (T)a.ph.scale[0], ru.im *= (T)a.ph.scale[0];
         rd.re *= (T)a.ph.scale[1], rd.im *= (T)a.ph.scale[1];
