@@ -141,7 +141,10 @@ F32::elem* links_of<F32>(mspcg_ctx* c) { return c->L32; }
 template <>
 F16::elem* links_of<F16>(mspcg_ctx* c) { return c->L16; }
 
-long hop_nparts(mspcg_ctx* c) { return hop_grid_x(c->Vh, c->Ls, 1, true); }
+template <class S>
+long hop_nparts(mspcg_ctx* c, bool cg) { return hop_grid_x<S>(c->Vh, c->Ls, 1, true, cg); }
+template long hop_nparts<F64>(mspcg_ctx*, bool);
+template long hop_nparts<F32>(mspcg_ctx*, bool);
 
 void pick_tile(const int pref[4], const Box& b, int out[4]) {
     bool any = false;
@@ -290,7 +293,7 @@ int op_mhatdag(mspcg_ctx* c, Field<S> q, CField<S> y, const int* done, hipStream
 // kernels: p = src + beta p rides on the first 5D kernel (t = B p), alpha =
 // (flexible ? zr : rr) / |Mhat p|^2 is formed after the Mhat half, and the last
 // hop does r -= alpha q, x += alpha p with |r|^2 partials (q stored only when
-// keep_q).  The caller follows with launch_cg_beta over hop_nparts partials.
+// keep_q).  The caller follows with launch_cg_beta over hop_nparts (cg) partials.
 template <class S>
 int cg_step(mspcg_ctx* c, Field<S> x, Field<S> r, Field<S> p, Field<S> q, CField<S> src,
             bool keep_q, bool flexible, const int* done, hipStream_t st) {
@@ -322,7 +325,7 @@ int cg_step(mspcg_ctx* c, Field<S> x, Field<S> r, Field<S> p, Field<S> q, CField
     if ((e = op_hop<S>(c, y, cfield(u), 0, false, prog_scale(-0.25), &pc, c->pr.M5, c->partials,
                        done, st)))
         return e;
-    if (launch_cg_alpha(c->sc, c->partials, (int)hop_nparts(c), st, flexible ? 1 : 0))
+    if (launch_cg_alpha(c->sc, c->partials, (int)hop_nparts<S>(c, false), st, flexible ? 1 : 0))
         return MSPCG_EHIP;
     if ((e = op_hop<S>(c, v, cfield(y), 1, true, c->pr.Xdag, nullptr, c->pr.id, nullptr, done, st)))
         return e;

@@ -178,7 +178,9 @@ struct CgUpdate {
 template <class S>
 int cg_step(mspcg_ctx* c, Field<S> x, Field<S> r, Field<S> p, Field<S> q, CField<S> src,
             bool keep_q, bool flexible, const int* done, hipStream_t st);
-long hop_nparts(mspcg_ctx* c);
+// workgroups (partial sums) of a whole-lattice hop
+template <class S>
+long hop_nparts(mspcg_ctx* c, bool cg);
 // traversal tile for a box: the largest even divisor of each extent that does
 // not exceed the preferred tile (all zero: lexicographic order)
 void pick_tile(const int pref[4], const Box& b, int out[4]);

@@ -9,11 +9,6 @@ MSPCG_HOP_WIDE(MSPCG_HOP_EXTERN, F16)
 template int launch_hop<F16>(const HopArgs<F16>&, int, int, bool, bool, hipStream_t,
                              const HopReach*);
 
-long hop_grid_x(long Vh, int Ls, int ndom, bool small) {
-    const int spb = small && hop_is_small(Vh, Ls, ndom) ? 64 / Ls : 256 / Ls;
-    return (Vh + spb - 1) / spb;
-}
-
 bool multi_hop_ls(int Ls) { return Ls == 8 || Ls == 12 || Ls == 16; }
 template int launch_multi_hop<F16>(const MultiHop<F16>*, long, int, bool, bool, bool,
                                     bool, hipStream_t);

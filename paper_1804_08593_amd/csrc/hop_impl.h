@@ -702,7 +702,7 @@ int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipS
     // FP16-storage hops address a domain's input sites with 32-bit offsets
     const long site_bytes = (long)Ls * Chunk<S>::K * 16;
     if (S::has_scale && (a.g.in.Vh >= (1L << 24) || a.g.in.Vh * site_bytes > 0xffffffffL)) return -1;
-    if (small && hop_is_small(a.site_list ? a.n_list : a.g.out.Vh, Ls, ndom)) {
+    if (small && hop_is_small<S>(a.site_list ? a.n_list : a.g.out.Vh, Ls, ndom, a.cg_r.data != nullptr)) {
         if (launch_hop_small<S>(a, Ls, ndom, dag, st)) return -1;
         return hipGetLastError() == hipSuccess ? 0 : -2;
     }

@@ -164,17 +164,42 @@ bool multi_hop_ls(int Ls);  // Ls handled by the multi-lattice kernel
 template <class S>
 int launch_multi_hop(const MultiHop<S>* dev, long items, int Ls, bool dag, bool eph, bool epa,
                      bool cg, hipStream_t st);
+// Whether a launch onto Vh sites of each of ndom domains (cg: with the fused update)
+// takes the small-launch kernel.  hop_body's time hardly depends on the size up to 65536
+// entries; the small kernel's steps up with every round of the workgroups that the CUs
+// hold at once, in FP64 2 a CU (1 at Ls = 24 and 32), in FP32 and FP16 3 (2 at Ls = 32,
+// and for FP16 with the update).  Microseconds of the four hops of a step, hop_body /
+// small, by workgroups:
+//   FP64, a second round still pays up to Ls = 12 and for single ones at Ls = 24:
+//     Ls = 8  256: 68 / 36, 512: 70 / 49, 640: 71 / 62; 12  512: 65 / 47, 640: 66 / 60
+//     Ls = 16 512: 63 / 52, 576: 62 / 65; 20  512: 62 / 50, 640: 62 / 64
+//     Ls = 24 256: 61 / 36, 512: 62 / 59, 640: 63 / 78; 32  256: 58 / 41, 320: 59 / 63
+//   FP32: 8  640: 55 / 37; 16  640: 50 / 40; 20  683: 49 / 40
+//     Ls = 24 768: 50 / 40, 800: 51 / 53; 32  512: 51 / 39, 640: 50 / 58
+//   FP16 without the update: 8  640: 35 / 27; 24  768: 35 / 30, 800: 33 / 40;
+//     32  512: 35 / 28, 640: 35 / 41; with it 8  512: 11 / 9, 640: 12 / 15;
+//     16  512: 11 / 10, 640: 11 / 15; 24  512: 11 / 9, 640: 11 / 15
+// Beyond 42000 entries a CG iteration in FP64 took 137 / 142 us at 12^4 x 8 and 156 / 188
+// at 12^4 x 12.
+template <class S>
+inline bool hop_is_small(long Vh, int Ls, int ndom, bool cg) {
+    const int spb = 64 / Ls;
+    const long groups = (Vh + spb - 1) / spb * ndom;
+    long most = 768;
+    if (sizeof(typename S::real) == 8) {
+        if (Ls > 12) most = Ls <= 24 ? 512 : 256;
+    } else if (Ls > 24 || (S::has_scale && cg)) {
+        most = 512;
+    }
+    return Vh * Ls * ndom <= 42000 && groups <= most;
+}
 // workgroups per domain for Vh output sites on each of ndom domains; small: the
 // small-launch kernel may be used
-long hop_grid_x(long Vh, int Ls, int ndom, bool small);
-// Whether a launch onto Vh sites of each of ndom domains takes the small-launch
-// kernel.  hop_body's time hardly depends on the size while every CU holds at most
-// one of its workgroups (65536 entries); the small kernel's grows with the size
-// from a lower start.  Microseconds per FP64 CG iteration (4 hops; hop_body /
-// small): 4^4x8 71 / 56, 8^4x8 (16384 entries) 97 / 61, 8^4x12 92 / 69, 8^4x16 90 /
-// 75, 8^3x16x8 (32768) 99 / 73, 8^4x24 (49152) 97 / 138, 8^3x16x16 (65536) 102 /
-// 112, 12^4x8 (82944) 137 / 142, 12^4x12 156 / 188.
-inline bool hop_is_small(long Vh, int Ls, int ndom) { return Vh * Ls * ndom <= 42000; }
+template <class S>
+inline long hop_grid_x(long Vh, int Ls, int ndom, bool small, bool cg) {
+    const int spb = small && hop_is_small<S>(Vh, Ls, ndom, cg) ? 64 / Ls : 256 / Ls;
+    return (Vh + spb - 1) / spb;
+}
 
 // Whether an FP16 block hop onto Vh sites of each of ndom domains takes the
 // matrix-core kernel (never one with the fused update, see there), and its workgroups per domain.  Ls = 16 fills the columns

@@ -397,9 +397,9 @@ static HopReach hop_reach(const Domains& D, const int* list) {
 template <class S>
 static long dom_hop_np(const Domains& D, const Box& out, long nlist, int Ls, bool alt) {
     const long n = nlist > 0 ? nlist : out.Vh;
-    if (alt && !hop_is_small(n, Ls, D.ndom) && hop_is_rows<S>(n, D.pad2.Vh, Ls, D.ndom))
+    if (alt && !hop_is_small<S>(n, Ls, D.ndom, false) && hop_is_rows<S>(n, D.pad2.Vh, Ls, D.ndom))
         return row_grid_x(out, D.ndom);
-    return hop_grid_x(n, Ls, D.ndom, alt);
+    return hop_grid_x<S>(n, Ls, D.ndom, alt, false);
 }
 
 // Arguments of one block-domain hop (every block in one launch) and its
@@ -597,7 +597,7 @@ static int local_init(mspcg_ctx* c, Local<S>& L) {
     const int spb = kThreads / Ls;
     L.start_np = (D.interior.Vh + spb - 1) / spb;
     // partials of the fused update: one per workgroup of the interior hop
-    L.upd_np = hop_grid_x(D.interior.Vh, Ls, D.ndom, L.alt);
+    L.upd_np = hop_grid_x<S>(D.interior.Vh, Ls, D.ndom, L.alt, true);
     const long vec_np = (nd + kThreads - 1) / kThreads;
     long need = L.hop_np > L.start_np ? L.hop_np : L.start_np;
     if (L.upd_np > need) need = L.upd_np;
@@ -845,7 +845,7 @@ struct BatchPrecondImpl : BatchPrecond {
                 }
                 h[k].a[j] = a;
                 h[k].ls[j] = G.Ls;
-                h[k].gx[j] = (int)hop_grid_x(nout, G.Ls, 1, false);
+                h[k].gx[j] = (int)hop_grid_x<S>(nout, G.Ls, 1, false, G.cgf[k]);
                 h[k].first[j] = first;
                 first += (long)L[i].c->dom.ndom * h[k].gx[j];
             }
@@ -963,11 +963,14 @@ size_t precond_partials_need(mspcg_ctx* c) {
     const Domains& D = c->dom;
     const int Ls = c->Ls;
     const long nd = D.interior.Vh * Ls;
-    long hop_np = 0;  // of every kernel and both reducing hops
+    long hop_np = 0;  // of every precision and kernel, both reducing hops
     for (const bool alt : {false, true})
         for (const long n : {dom_hop_np<F64>(D, D.ybox(), D.yn(), Ls, alt),
+                             dom_hop_np<F32>(D, D.ybox(), D.yn(), Ls, alt),
                              dom_hop_np<F16>(D, D.ybox(), D.yn(), Ls, alt),
-                             hop_grid_x(D.interior.Vh, Ls, D.ndom, alt)})
+                             hop_grid_x<F64>(D.interior.Vh, Ls, D.ndom, alt, true),
+                             hop_grid_x<F32>(D.interior.Vh, Ls, D.ndom, alt, true),
+                             hop_grid_x<F16>(D.interior.Vh, Ls, D.ndom, alt, true)})
             if (n > hop_np) hop_np = n;
     const int spb = kThreads / Ls;
     const long start_np = (D.interior.Vh + spb - 1) / spb;

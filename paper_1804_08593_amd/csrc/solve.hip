@@ -158,7 +158,7 @@ struct CGSolver : Solver {
         pp = half_field<F64>(c, "d.cg_p", c->Nh);
         q = half_field<F64>(c, "d.cg_q", c->Nh);
         if (!r.data || !pp.data || !q.data) return MSPCG_ENOMEM;
-        nph = hop_nparts(c);
+        nph = hop_nparts<F64>(c, true);
         npb = blas_grid_x(12 * c->Nh);
         int e;
         if ((e = ensure_partials(c, 4 * (nph > npb ? nph : npb) + 16))) return e;
@@ -242,7 +242,7 @@ struct MSPCGSolver : Solver {
         if (!r.data || !pp.data || !q.data || !z.data) return MSPCG_ENOMEM;
         int e;
         if ((e = domains_setup(c, p->blocking, p->inner_prec, st))) return e;
-        nph = hop_nparts(c);
+        nph = hop_nparts<F64>(c, true);
         npb = blas_grid_x(12 * c->Nh);
         size_t need = 4 * (size_t)(nph > npb ? nph : npb) + 16;
         const size_t pneed = precond_partials_need(c);
@@ -354,7 +354,7 @@ struct MixedSolver : Solver {
         qs = half_field<F32>(c, "s.cg_q", c->Nh);
         xs = half_field<F32>(c, "s.cg_x", c->Nh);
         if (!r.data || !rs.data || !ps.data || !qs.data || !xs.data) return MSPCG_ENOMEM;
-        nph = hop_nparts(c);
+        nph = hop_nparts<F32>(c, true);
         npb = blas_grid_x(12 * c->Nh);
         int e;
         if ((e = ensure_partials(c, 4 * (size_t)(nph > npb ? nph : npb) + 16))) return e;
