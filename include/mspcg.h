@@ -162,7 +162,11 @@ typedef struct {
  * the preferred tile for precision p (MSPCG_FP64/FP32/FP16; all zero =
  * lexicographic order; each extent is reduced to the largest even divisor of
  * the box extent).  xcd_remap = 1 gives each of the 8 XCDs one contiguous
- * range of tiles. */
+ * range of tiles.  Three kinds of launch have an order of their own and ignore
+ * the tile: those onto few sites (up to 42000 site-slices over all blocks, or
+ * fewer, by precision and Ls), block hops onto a part of the widened block (the
+ * middle two of a local step with pad > 0), and large FP16 block hops at Ls = 16
+ * other than the one with the local CG update. */
 typedef struct {
     int xcd_remap;
     int tile[3][4];
@@ -318,8 +322,9 @@ int mspcg_get_tuning(mspcg_ctx* ctx, mspcg_tuning* tuning);
 int mspcg_set_tuning(mspcg_ctx* ctx, const mspcg_tuning* tuning);
 
 /* Autotuner: times candidate traversal tiles and the XCD remap on this
- * context's lattice (A in FP64 and FP32; the block operator in FP16 when
- * blocking is not NULL) with HIP events and keeps the fastest.  Results are
+ * context's lattice (A in FP64 and FP32; when blocking is not NULL, the FP16
+ * block hops of a local step that follow the tile in mspcg_solve; where none
+ * does, the FP16 tile stays as it was) with HIP events and keeps the fastest.  Results are
  * cached per (dims, Ls, blocking) in the text file cache_path when it is not
  * NULL (read first, appended after tuning; a cached line whose tiles
  * mspcg_set_tuning would reject is skipped).  Needs the gauge field. */

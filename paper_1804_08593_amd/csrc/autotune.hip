@@ -1,6 +1,6 @@
 // Autotuner for the hop traversal: times candidate 4D tiles and the XCD
-// remap on the context's own lattice (A in FP64 / FP32, the block operator
-// in the local-solve precision) with HIP events, keeps the fastest, and
+// remap on the context's own lattice (A in FP64 / FP32, the FP16 block hops of
+// a local step that follow the tile) with HIP events, keeps the fastest, and
 // caches the choice per (dims, Ls, blocking) in a plain text file.
 #include <math.h>
 #include <stdio.h>
@@ -158,31 +158,34 @@ extern "C" int mspcg_autotune(mspcg_ctx* c, const mspcg_blocking* bk, const char
         c->tune = t;
     }
     t.xcd_remap = best_remap;
-    // block operator of the local solves (FP16 storage)
+    // block hops of the local solves (FP16 storage); the tile stays as it was where
+    // none of them follows it
     if (bk) {
         c->tune = t;
         if ((e = domains_setup(c, *bk, MSPCG_FP16, st))) return e;
         const Domains& D = c->dom;
         const long n = (long)D.ndom * D.interior.Vh * c->Ls;
         Field<F16> p = half_field<F16>(c, "dom16.p", n);
-        Field<F16> w = half_field<F16>(c, "dom16.w", n);
-        if (!p.data || !w.data) return MSPCG_ENOMEM;
+        Field<F16> rho = half_field<F16>(c, "dom16.rho", n);
+        double* al = (double*)c->buf("in.a", D.ndom * sizeof(double));
+        if (!p.data || !rho.data || !al) return MSPCG_ENOMEM;
         MSPCG_HIP(hipMemsetAsync(p.data, 0, (size_t)12 * n * sizeof(__half2), st));
         MSPCG_HIP(hipMemsetAsync(p.scale, 0, (size_t)n * sizeof(float), st));
-        float best = 1e30f;
-        Cand bc = cands[0];
+        MSPCG_HIP(hipMemsetAsync(al, 0, D.ndom * sizeof(double), st));
+        // every field of a local step filled (zeros)
+        if ((e = block_A<F16>(c, rho, cfield(p), nullptr, nullptr, st))) return e;
+        double best = 1e30;
         for (const Cand& cd : cands) {
             if (cd.remap != t.xcd_remap) continue;
             memcpy(c->tune.tile[MSPCG_FP16], cd.tile, sizeof(cd.tile));
-            float ms = 0;
-            if ((e = time_ms(st, reps, [&] { return block_A<F16>(c, w, cfield(p), nullptr, nullptr, st); }, ms)))
-                return e;
+            double ms = 0;
+            if ((e = local_tile_hops<F16>(c, reps, st, ms)) < 0) return e;
+            if (e == 0) break;
             if (ms < best) {
                 best = ms;
-                bc = cd;
+                memcpy(t.tile[MSPCG_FP16], cd.tile, sizeof(cd.tile));
             }
         }
-        memcpy(t.tile[MSPCG_FP16], bc.tile, sizeof(bc.tile));
     }
     c->tune = t;
     c->timing = was_timing;

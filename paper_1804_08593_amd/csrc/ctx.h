@@ -219,6 +219,14 @@ struct BatchPrecond {
 };
 int make_batch_precond(mspcg_ctx* const* cs, int n, int prec, int l, const int* const* done,
                        bool multi, std::unique_ptr<BatchPrecond>& out);
+// For the autotuner: `reps` local steps on whatever the local solves' fields hold (step
+// 0 of 2: the fused update without z), ms = the time of the hops among them that visit
+// their sites in the order of the traversal tile.  Whole steps, because those hops alone,
+// one after another, find their inputs in cache (24^3x48x16 in two blocks: they then ask
+// for 24x4x8x16, 327 us a hop in a solve against 319 in lexicographic order).  Returns
+// the number of such hops a step, or a negative error.
+template <class S>
+int local_tile_hops(mspcg_ctx* c, int reps, hipStream_t st, double& ms);
 // w = A_s p on every block (domain layout, precision S)
 template <class S>
 int block_A(mspcg_ctx* c, Field<S> w, CField<S> p, double* partials, const int* done,

@@ -214,6 +214,15 @@ template <class S>
 inline bool hop_is_rows(long Vh, long widest, int Ls, int ndom) {
     return S::has_scale && Ls == 16 && Vh * ndom >= 150000 && widest * Ls * 48 < 0x70000000;
 }
+// Whether a block hop visits its sites in the order of the traversal tile: the general
+// kernel onto a whole box
+template <class S>
+inline bool hop_follows_tile(const HopArgs<S>& a, int Ls, int ndom, bool small,
+                             const HopReach* reach) {
+    if (a.site_list) return false;
+    if (small && hop_is_small<S>(a.g.out.Vh, Ls, ndom, a.cg_r.data != nullptr)) return false;
+    return !(reach && !a.cg_r.data && hop_is_rows<S>(a.g.out.Vh, reach->widest, Ls, ndom));
+}
 constexpr int kRowWaves = 4;  // waves (strip pieces) of a workgroup
 inline long row_grid_x(const Box& out, int ndom) {
     const int n = row_chunk(out, ndom);

@@ -786,6 +786,47 @@ static int precond_core(mspcg_ctx* c, int l, CField<F64> r, Field<F64> z, const 
     return local_finish<S>(L, l, z, dots, st);
 }
 
+template <class S>
+int local_tile_hops(mspcg_ctx* c, int reps, hipStream_t st, double& ms) {
+    Local<S> L;
+    int e, n = 0;
+    if ((e = local_init<S>(c, L))) return e;
+    const bool was = c->timing;
+    timing_reset(c);
+    auto steps = [&]() -> int {
+        for (int r = 0; r <= reps; ++r) {  // the first one untimed
+            if ((e = local_B<S>(L, 0, nullptr, st))) return e;
+            n = 0;
+            for (int k = 0; k < 4; ++k) {
+                double bytes;
+                bool dag;
+                const HopArgs<S> a = local_hop<S>(L, k, 0, 2, nullptr, bytes, dag);
+                const HopReach reach = hop_reach(c->dom, a.site_list);
+                const bool follows = hop_follows_tile(a, c->Ls, c->dom.ndom, L.alt, &reach);
+                n += follows;
+                c->timing = follows && r > 0;
+                Timed t(c, MSPCG_KC_HOPDOM, bytes, st);
+                c->timing = false;
+                if (launch_hop<S>(a, c->Ls, c->dom.ndom, dag, L.alt, st, &reach)) return MSPCG_EHIP;
+            }
+        }
+        MSPCG_HIP(hipStreamSynchronize(st));
+        ms = 0;
+        for (const TimingRec& r : c->trecs) {
+            float t = 0;
+            MSPCG_HIP(hipEventElapsedTime(&t, r.a, r.b));
+            ms += t;
+        }
+        return 0;
+    };
+    c->timing = false;
+    e = steps();
+    timing_reset(c);
+    c->timing = was;
+    return e ? e : n;
+}
+template int local_tile_hops<F16>(mspcg_ctx*, int, hipStream_t, double&);
+
 // Local solves of several lattices interleaved stage by stage; with `multi`
 // every block-hop stage runs as one persistent launch per group of lattices
 // that share Ls (MultiHop), otherwise one launch per lattice.

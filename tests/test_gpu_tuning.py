@@ -97,3 +97,34 @@ def test_tune_blocking_short_probe_and_full_solves():
     with pytest.raises(mspcg.MspcgError) as e:
         ctx.tune_blocking(base, probe_iters=-1)
     assert e.value.code == mspcg.EINVAL
+
+
+@pytest.mark.parametrize("dims,Ls,blk,follows", [
+    ((4, 4, 4, 8), 8, (4, 4, 4, 4), False),          # every hop a launch onto few sites
+    ((8, 8, 8, 8), 8, (4, 4, 4, 4), True),           # the first hop on the general kernel
+    ((24, 24, 24, 24), 16, (12, 12, 12, 12), True),  # the hop with the update alone
+], ids=lambda v: str(v))
+def test_autotune_scores_fp16_tiles_on_the_hops_that_follow_them(dims, Ls, blk, follows):
+    """The FP16 tile is chosen among the candidates by hops that read it, and stays as
+    it was where no block hop of a solve does."""
+    ctx = mspcg.Context(dims, Ls, 1.8, 0.05, 1.5, 0.5)
+    ctx.load_gauge(dev(synth.unit_gauge(dims)))
+    own = [6, 2, 2, 2]  # not a candidate
+    t = ctx.get_tuning().as_dict()["tile"]
+    ctx.set_tuning(1, t["fp64"], t["fp32"], own)
+    got = ctx.autotune(blk, 2)["tile"]["fp16"]
+    say(dims, Ls, blk, "fp16 tile", got)
+    assert (got != own) == follows
+    # a local solve after it starts from its own fields: as on a fresh context with
+    # the same tuning
+    r = torch.randn(ctx.fshape, dtype=torch.complex128, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(5))
+    z, ref = torch.zeros_like(r), torch.zeros_like(r)
+    for out, c in ((z, ctx), (ref, mspcg.Context(dims, Ls, 1.8, 0.05, 1.5, 0.5))):
+        if c is not ctx:
+            c.load_gauge(dev(synth.unit_gauge(dims)))
+            u = ctx.get_tuning()
+            c.set_tuning(u.xcd_remap, *(list(u.tile[k]) for k in range(3)))
+        c.set_blocking(blk, 2)
+        c.precond(r, out, 2, prec=mspcg.FP16)
+    assert torch.equal(z, ref)
