@@ -259,8 +259,8 @@ int mspcg_apply(mspcg_ctx* ctx, int op, int prec, const void* in_dev, void* out_
  * context's gauge field must already be loaded.  Its intermediate fields
  * live in one fixed scratch array per GPU of MSPCG_NOALLOC_SCRATCH_BYTES,
  * held by the library from load to process end, instead of context
- * buffers; no hipMalloc, hipFree or other allocating call is made.  An
- * application needs 8 one-parity fields, 8 * (V4/2) * Ls * 12 * 16 bytes in
+ * buffers; no hipMalloc, hipFree or other allocating call is made.  The
+ * scratch must hold 8 one-parity fields, 8 * (V4/2) * Ls * 12 * 16 bytes in
  * FP64 (half in FP32), each rounded up to 256 bytes; a larger lattice is
  * rejected with MSPCG_ESCRATCH before any work is queued (FP64 reaches
  * V4 * Ls = 174762, e.g. 8^3x16 at Ls = 16).  Every call on one GPU shares
@@ -324,9 +324,9 @@ int mspcg_set_tuning(mspcg_ctx* ctx, const mspcg_tuning* tuning);
 /* Autotuner: times candidate traversal tiles and the XCD remap on this
  * context's lattice (A in FP64 and FP32; when blocking is not NULL, the FP16
  * block hops of a local step that follow the tile in mspcg_solve; where none
- * does, the FP16 tile stays as it was) with HIP events and keeps the fastest.  Results are
- * cached per (dims, Ls, blocking) in the text file cache_path when it is not
- * NULL (read first, appended after tuning; a cached line whose tiles
+ * does, the FP16 tile stays as it was) with HIP events and keeps the fastest.
+ * Results are cached per (dims, Ls, blocking) in the text file cache_path when
+ * it is not NULL (read first, appended after tuning; a cached line whose tiles
  * mspcg_set_tuning would reject is skipped).  Needs the gauge field. */
 int mspcg_autotune(mspcg_ctx* ctx, const mspcg_blocking* blocking, const char* cache_path,
                    hipStream_t stream);

@@ -77,8 +77,6 @@ struct Domains {
     const int* ylist() const { return form == MSPCG_FORM_SPLIT ? nullptr : list_y; }
     long yn() const { return form == MSPCG_FORM_SPLIT ? 0 : n_y; }
     long yread() const { return form == MSPCG_FORM_SPLIT ? 0 : rd_y; }
-    // output sites of the y hop (its partials count)
-    long yout() const { return ylist() ? n_y : ybox().Vh; }
 };
 
 }  // namespace mspcg

@@ -57,21 +57,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int by
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
 }
 
-// y[i] += c * (x[i] of the lane that the DPP control selects; 0 beyond the row's
+// y[i] += c * (y[i] of the lane that the DPP control selects; 0 beyond the row's
 // end), as one instruction each.  Written out because the compiler keeps the
 // lane move and the multiply-add apart.  s_nop 1: the two wait states between
 // a vector write and its read through DPP.
 #define MSPCG_ROW_FMAC(NAME, CTRL)                                                                \
-    template <int N>                                                                              \
-    __device__ __forceinline__ void NAME(float (&y)[4], const float (&x)[4], float c) {           \
-        asm("s_nop 1\n\t"                                                                         \
-            "v_fmac_f32_dpp %0, %4, %8 " CTRL ":%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"   \
-            "v_fmac_f32_dpp %1, %5, %8 " CTRL ":%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"   \
-            "v_fmac_f32_dpp %2, %6, %8 " CTRL ":%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"   \
-            "v_fmac_f32_dpp %3, %7, %8 " CTRL ":%9 row_mask:0xf bank_mask:0xf bound_ctrl:1"       \
-            : "+&v"(y[0]), "+&v"(y[1]), "+&v"(y[2]), "+&v"(y[3])                                  \
-            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(c), "n"(N));                        \
-    }                                                                                             \
     template <int N>                                                                              \
     __device__ __forceinline__ void NAME(float (&y)[4], float c) {                                \
         asm("s_nop 1\n\t"                                                                         \

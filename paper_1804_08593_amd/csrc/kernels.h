@@ -122,10 +122,11 @@ struct RowArgs {
     const int* done;
 };
 
-// x extent of a strip piece of the FP16 matrix-core hop.  A piece loads two
-// slices of inputs beyond its own, so it has at least 4 steps where the box
-// does; 6144 pieces are two rounds of the 3 waves per SIMD that its
-// registers allow, so that the last round costs little.
+// x extent of a strip piece of the FP16 matrix-core hop (the last piece of a strip
+// takes what is left, 2 at the least).  A piece loads two slices of inputs beyond its
+// own, so pieces are cut no shorter than 4 where the box is that long; 6144 pieces are
+// two rounds of the 3 waves per SIMD that its registers allow, so that the last round
+// costs little.
 inline int row_chunk(const Box& out, int ndom) {
     const long strips = (long)out.E[1] * out.E[2] * out.E[3] / 8 * ndom;
     int n = out.E[0];

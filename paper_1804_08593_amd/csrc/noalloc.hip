@@ -16,8 +16,8 @@ namespace {
 __device__ __align__(256) unsigned char scratch[MSPCG_NOALLOC_SCRATCH_BYTES];
 
 constexpr int kMaxDevices = 64;
-// an application of A needs 8 one-parity fields: in/out of both parities
-// and the 4 intermediates of Mhat^+ Mhat
+// lattices whose 8 one-parity fields fit are accepted, whatever the operators need of
+// them (A, the most: its input and the 4 intermediates of Mhat^+ Mhat)
 constexpr size_t kFields = 8;
 
 std::mutex g_mu;

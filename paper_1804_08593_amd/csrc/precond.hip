@@ -974,7 +974,10 @@ static int make_batch_impl(mspcg_ctx* const* cs, int n, int l, const int* const*
     b->done.assign(done, done + n);
     int e;
     // where the persistent launches are possible, their workgroups set the order
-    // of the sums and both forms of the batch use them
+    // of the sums and both forms of the batch use them, so that they agree to the last
+    // bit; the batch then does without the small-launch and matrix-core hops of
+    // mspcg_solve (8^4x8 14.8 ms in a batch of its own against 12.1, 12^4x12 28.5 against
+    // 28.0, and within 1% for 12^3x24x8, 16^4x16, 16^3x32x12 and 20^4x16)
     bool all = true;
     for (int i = 0; i < n; ++i) all = all && multi_hop_ls(cs[i]->Ls);
     for (int i = 0; i < n; ++i) {
