@@ -284,6 +284,21 @@ __host__ __device__ constexpr int link_slot(int dir, int k) {
     return S::has_scale ? ((dir & 3) * 9 + k) * 2 + (dir >> 2) : dir * 9 + k;
 }
 
+// the 9 entries of the forward and of the backward link of one mu, as stored in FP16
+// (__half2 each, side by side); p: the first, 8-byte aligned
+__device__ __forceinline__ void link_pairs(const unsigned* p, unsigned (&f)[9], unsigned (&b)[9]) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    typedef nt_u4 u4a8 __attribute__((aligned(8)));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const nt_u4 t = *reinterpret_cast<const u4a8*>(p + 4 * k);
+        f[2 * k] = t.x, b[2 * k] = t.y;
+        f[2 * k + 1] = t.z, b[2 * k + 1] = t.w;
+    }
+    const u2 t = *reinterpret_cast<const u2*>(p + 16);
+    f[8] = t.x, b[8] = t.y;
+}
+
 template <class S, bool NT = false>
 __device__ __forceinline__ cx<typename S::real> load_link(const typename S::elem* p) {
     if constexpr (S::has_scale) {

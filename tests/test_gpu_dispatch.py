@@ -104,6 +104,27 @@ def test_boundary_fields_written_by_the_general_hop(dims, Ls, prec):
             assert np.all(O.parity_mask(act, got, 1) == 0)
 
 
+@pytest.mark.parametrize("dims,block,Ls", [
+    ((16, 12, 12, 20), (16, 12, 6, 10), 2),  # links loaded by every thread, not staged
+    ((16, 12, 12, 10), (8, 12, 12, 10), 4),
+    ((12, 10, 12, 10), (6, 10, 12, 10), 6),
+    ((8, 8, 10, 6), (4, 8, 10, 6), 24),
+    ((8, 8, 6, 8), (8, 8, 6, 4), 32),
+], ids=lambda v: str(v))
+def test_fp16_block_operator_on_the_general_hop(dims, block, Ls):
+    assert entries(dims, Ls) > SMALL_MOST
+    act, U, ctx = setup(dims, Ls, 1.8, 0.05, 1.5, 0.5, gseed=61)
+    p = O.parity_mask(act, synth.fermion_field(dims, Ls, 62), 0)
+    for pad, mode in ((0, "dirichlet"), (2, "literal")):
+        ctx.set_blocking(block, pad)
+        out = torch.full_like(dev(p), float("nan"))
+        ctx.apply(mspcg.OP_KBLOCK, dev(p), out, prec=mspcg.FP16)
+        ref = O.block_precond_op(act, U, p, block, mode)
+        err, se = relerr(host(out), ref), site_err(host(out), ref)
+        say(f"K {dims} {block} pad={pad} Ls={Ls}: {err:.2e} per entry {se:.2e}")
+        assert err <= k16_bars()[0] and se <= k16_bars()[1]
+
+
 @pytest.mark.parametrize("prec", [mspcg.FP64, mspcg.FP32, mspcg.FP16])
 @pytest.mark.parametrize("dims,block,pad,Ls", [
     # u onto 82944 entries general, the last hop onto 16384 small

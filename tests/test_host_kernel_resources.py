@@ -1,6 +1,5 @@
-"""Registers of compiled kernels (no GPU): what decides how many workgroups of the
-small-launch hop a CU holds."""
-import os
+"""Compiled kernels (no GPU): the registers that decide how many workgroups of the
+small-launch hop a CU holds; how the FP16 hop at Ls = 2 loads its links."""
 import re
 import subprocess
 
@@ -14,17 +13,23 @@ WORKGROUPS = {("F64", 6): 2, ("F64", 8): 2, ("F64", 12): 2, ("F64", 16): 2, ("F6
               ("F32", 16): 3, ("F32", 20): 3, ("F32", 24): 3}
 
 
-def _vgprs(tmp_path, cases):
+def _listing(tmp_path, header, kernels):
     src = tmp_path / "k.hip"
-    src.write_text('#include "hop_small.h"\nnamespace mspcg {\n' + "".join(
-        f"template __global__ void hop_small_kernel<{p}, {ls}, true, {cg}>(HopArgs<{p}>);\n"
-        for p, ls in cases for cg in ("true", "false")) + "}\n")
+    src.write_text(f'#include "{header}"\nnamespace mspcg {{\n' +
+                   "".join(f"template __global__ void {k};\n" for k in kernels) + "}\n")
     r = subprocess.run(["hipcc", *build.CXXFLAGS, "-I", build.CSRC, "--cuda-device-only", "-S", str(src),
                         "-o", str(tmp_path / "k.s")], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
+    return (tmp_path / "k.s").read_text()
+
+
+def _vgprs(tmp_path, cases):
+    text = _listing(tmp_path, "hop_small.h",
+                    [f"hop_small_kernel<{p}, {ls}, true, {cg}>(HopArgs<{p}>)"
+                     for p, ls in cases for cg in ("true", "false")])
     out = {}
     name = None
-    for ln in (tmp_path / "k.s").read_text().splitlines():
+    for ln in text.splitlines():
         m = re.match(r"\s*\.amdhsa_kernel \S*hop_small_kernelINS_3(F\d\d)ELi(\d+)ELb1ELb([01])E", ln)
         if m:
             name = (m[1], int(m[2]), m[3] == "1")
@@ -42,3 +47,14 @@ def test_small_hop_with_fused_update_keeps_its_residency(tmp_path, prec):
     for k in cases:
         room = 512 // (2 * WORKGROUPS[k]) // 8 * 8
         assert v[(*k, False)] <= room and v[(*k, True)] <= room, (k, v)
+
+
+def test_fp16_hop_loads_unstaged_links_in_wide_loads(tmp_path):
+    """At Ls = 2 the links do not fit in LDS beside each other and every thread loads its
+    72 entries: the two directions of a mu in five loads, not 4 bytes at a time."""
+    text = _listing(tmp_path, "hop_impl.h",
+                    ["hop_kernel<F16, 2, false, false, false, false>(HopArgs<F16>)"])
+    loads = re.findall(r"\b(global|flat)_load_(\w+)", text)
+    single = sum(w in ("dword", "ushort", "short_d16", "short_d16_hi") for _, w in loads)
+    assert single <= 16, single  # scales and arguments
+    assert len(loads) <= 64, len(loads)
