@@ -717,7 +717,8 @@ int launch_hop(const HopArgs<S>& a, int Ls, int ndom, bool dag, bool small, hipS
     }
     if constexpr (S::has_scale) {
         if (reach && !a.cg_r.data &&
-            hop_is_rows<S>(a.site_list ? a.n_list : a.g.out.Vh, reach->widest, Ls, ndom)) {
+            hop_is_rows<S>(a.site_list ? a.n_list : a.g.out.Vh, reach->inner, reach->widest, Ls,
+                           ndom)) {
             if (launch_hop_rows(a, Ls, ndom, dag, *reach, st)) return -1;
             return hipGetLastError() == hipSuccess ? 0 : -2;
         }

@@ -105,7 +105,7 @@ inline bool row_prog_of(const FiveDProg& p, bool dag, double mf, int Ls, RowProg
 // distance) of the block of extent blk (0: not cut) at the domain origin; every one
 // when dist < 0.
 struct HopReach {
-    long widest;  // sites of the largest box of a domain
+    long inner, widest;  // sites of the block and of the largest box of a domain
     int dist, blk[4];
 };
 
@@ -203,17 +203,24 @@ inline long hop_grid_x(long Vh, int Ls, int ndom, bool small, bool cg) {
 }
 
 // Whether an FP16 block hop onto Vh sites of each of ndom domains takes the
-// matrix-core kernel (never one with the fused update, see there), and its workgroups per domain.  Ls = 16 fills the columns
-// of its matrix instruction (with Ls = 12 in them, 24^4 in 12^4 blocks, six local
-// steps took 6138 us against the general kernel's 5657).  It needs enough sites
-// for strips of some length on every wave slot: 16^3 x 32 (65536 sites) in 8^3 x 16
-// blocks 3177 against 2999 us, 24^4 (165888) in 12^4 blocks 6701 against 6763, in
-// two 24 x 24 x 12 x 24 blocks 5353 against 5536, 24^3 x 48 (331776) in two blocks
-// 10491 against 11178.  A field's part of the largest box (`widest` sites) stays
-// below the reach of its 32-bit offsets.
+// matrix-core kernel (never one with the fused update, see there); inner, widest: sites
+// of a block and of the largest box of a domain.  Ls = 16 fills the columns of its matrix
+// instruction (with Ls = 12 in them, 24^4 in 12^4 blocks, six local steps took 6138 us
+// against the general kernel's 5657).  It needs enough sites for strips of some length
+// on every wave slot, and it walks whole boxes in strips and forms absent neighbours as
+// zeros, where the general kernel leaves out both the corners and the neighbours: in
+// small blocks most of the widened box is rim.  Hops u + y + v of a step, general /
+// matrix-core us (block: part of its widened box): in favour 24^4 in 12^4 (0.32) 780 /
+// 713, in 6x12x12x24 (0.34) 758 / 656, in two blocks (0.75) 514 / 434, 24^3x48 in 12^3x24
+// (0.36) 1372 / 1201, in 8^3x16 (0.24) 1622 / 1517, 16x24x28x32 in 4x12x14x16 (0.23) 919 /
+// 884; against 24^4 in 8^4 (0.20) 911 / 924, in 6^4 (0.13) 1086 / 1171, in 4^4 (0.06)
+// 1553 / 2149, and with fewer sites in the blocks 16^3x32 (65536) in 8^4 364 / 416,
+// 20^4 (80000) in 10^4 (0.26) 387 / 419.  A field's part of the largest box stays below
+// the reach of its 32-bit offsets.
 template <class S>
-inline bool hop_is_rows(long Vh, long widest, int Ls, int ndom) {
-    return S::has_scale && Ls == 16 && Vh * ndom >= 150000 && widest * Ls * 48 < 0x70000000;
+inline bool hop_is_rows(long Vh, long inner, long widest, int Ls, int ndom) {
+    return S::has_scale && Ls == 16 && Vh * ndom >= 150000 && inner * ndom >= 90000 &&
+           5 * inner >= widest && widest * Ls * 48 < 0x70000000;
 }
 // Whether a block hop visits its sites in the order of the traversal tile: the general
 // kernel onto a whole box
@@ -222,7 +229,7 @@ inline bool hop_follows_tile(const HopArgs<S>& a, int Ls, int ndom, bool small,
                              const HopReach* reach) {
     if (a.site_list) return false;
     if (small && hop_is_small<S>(a.g.out.Vh, Ls, ndom, a.cg_r.data != nullptr)) return false;
-    return !(reach && !a.cg_r.data && hop_is_rows<S>(a.g.out.Vh, reach->widest, Ls, ndom));
+    return !(reach && !a.cg_r.data && hop_is_rows<S>(a.g.out.Vh, reach->inner, reach->widest, Ls, ndom));
 }
 constexpr int kRowWaves = 4;  // waves (strip pieces) of a workgroup
 inline long row_grid_x(const Box& out, int ndom) {

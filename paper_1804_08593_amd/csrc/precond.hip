@@ -386,6 +386,7 @@ static double hop_read_sites(const Box& in, const Box& out) {
 
 static HopReach hop_reach(const Domains& D, const int* list) {
     HopReach r;
+    r.inner = D.interior.Vh;
     r.widest = D.pad2.Vh;
     r.dist = !list ? -1 : (list == D.list_y ? 2 : 1);
     for (int m = 0; m < 4; ++m) r.blk[m] = D.nb[m] > 1 ? D.blk[m] : 0;
@@ -397,7 +398,8 @@ static HopReach hop_reach(const Domains& D, const int* list) {
 template <class S>
 static long dom_hop_np(const Domains& D, const Box& out, long nlist, int Ls, bool alt) {
     const long n = nlist > 0 ? nlist : out.Vh;
-    if (alt && !hop_is_small<S>(n, Ls, D.ndom, false) && hop_is_rows<S>(n, D.pad2.Vh, Ls, D.ndom))
+    if (alt && !hop_is_small<S>(n, Ls, D.ndom, false) &&
+        hop_is_rows<S>(n, D.interior.Vh, D.pad2.Vh, Ls, D.ndom))
         return row_grid_x(out, D.ndom);
     return hop_grid_x<S>(n, Ls, D.ndom, alt, false);
 }

@@ -1,5 +1,6 @@
 """The rules that choose a hop kernel (no GPU), compiled for the host from the
 library's own header."""
+import math
 import subprocess
 
 import pytest
@@ -32,6 +33,11 @@ template <class S> static void line(long vh, int Ls, int ndom, int cg) {
            hop_grid_x<S>(vh, Ls, ndom, false, cg));
 }
 int main(int n, char** v) {
+    if (!strcmp(v[1], "rows")) {  // outputs, block, largest box, domains
+        for (int i = 2; i + 3 < n; i += 4)
+            printf("%d\\n", (int)hop_is_rows<F16>(atol(v[i]), atol(v[i + 1]), atol(v[i + 2]), 16, atoi(v[i + 3])));
+        return 0;
+    }
     for (int i = 1; i + 4 < n; i += 5) {
         const long vh = atol(v[i + 1]);
         const int Ls = atoi(v[i + 2]), nd = atoi(v[i + 3]), cg = atoi(v[i + 4]);
@@ -69,3 +75,28 @@ def test_small_launch_hop_counts_every_domain(rules):
         assert (a, b, c) == (1, 0, 1)
     # never beyond 42000 entries
     assert rules([("F32", 5251, 8, 1, 0), ("F32", 5250, 8, 1, 0)]) == [(0, 165, 165), (1, 657, 165)]
+
+
+def _boxes(dims, block, pad=2):
+    """Sites of one parity: widened by 1, the block, widened by pad; domains."""
+    def vol(k):
+        return math.prod(L if L == b else b + 2 * k for L, b in zip(dims, block)) // 2
+    return vol(min(pad, 1)), vol(0), vol(pad), math.prod(L // b for L, b in zip(dims, block))
+
+
+@pytest.mark.parametrize("dims,block,pad,want", [
+    ((24, 24, 24, 24), (12, 12, 12, 12), 2, 1), ((24, 24, 24, 48), (12, 12, 12, 24), 2, 1),
+    ((24, 24, 24, 48), (24, 12, 24, 48), 2, 1), ((24, 24, 24, 24), (24, 24, 24, 24), 2, 1),
+    ((16, 24, 28, 32), (4, 12, 14, 16), 2, 1), ((24, 24, 24, 24), (4, 4, 4, 4), 0, 1),
+    # most of the widened blocks is rim
+    ((24, 24, 24, 24), (8, 8, 8, 8), 2, 0), ((24, 24, 24, 24), (6, 6, 6, 6), 2, 0),
+    ((24, 24, 24, 48), (4, 4, 4, 4), 2, 0), ((16, 16, 16, 32), (4, 4, 4, 8), 2, 0),
+    # too few sites in the blocks themselves
+    ((20, 20, 20, 20), (10, 10, 10, 10), 2, 0), ((16, 16, 16, 32), (8, 8, 8, 8), 2, 0),
+    ((32, 8, 8, 64), (16, 4, 4, 32), 2, 0),
+    # too few outputs
+    ((16, 16, 16, 40), (16, 16, 16, 20), 2, 0),
+], ids=str)
+def test_matrix_core_hop_is_chosen_where_blocks_fill_their_boxes(rules, dims, block, pad, want):
+    out, inner, widest, nd = _boxes(dims, block, pad)
+    assert rules([("rows", out, inner, widest, nd)]) == [(want,)]
