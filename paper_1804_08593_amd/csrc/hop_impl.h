@@ -277,7 +277,8 @@ struct HopShape {
     // entry (site, s, c) at (site * 12 + c) * LSP + s, so the lanes of a site
     // (consecutive s) and the chain threads (consecutive c) both hit distinct banks
     static constexpr int LSP = LS + 1;
-    // FP16 links are decoded to FP32 once, when staged; LE is the LDS entry
+    // FP16 links are decoded to FP32 and put in order (direction * 9 + entry) once, when
+    // staged; LE is the LDS entry
     using LE = typename std::conditional<S::has_scale, nt_f2, E>::type;
     static constexpr int NCH = 72 * (int)sizeof(E) / 16;   // 16-byte chunks of one site's links
     static constexpr int LSTR = 72 * (int)sizeof(LE) / 16 + 1;  // padded LDS site stride (chunks)
@@ -369,9 +370,11 @@ __device__ __forceinline__ void hop_body(const HopArgs<S>& a, int bx, int d, int
                 if constexpr (S::has_scale) {
                     const cx<float> e0 = h2f(v.x, 1.f), e1 = h2f(v.y, 1.f);
                     const cx<float> e2 = h2f(v.z, 1.f), e3 = h2f(v.w, 1.f);
-                    nt_f4* dst = reinterpret_cast<nt_f4*>(lnk + sl * LSTR + 2 * j);
-                    dst[0] = nt_f4{e0.re, e0.im, e1.re, e1.im};
-                    dst[1] = nt_f4{e2.re, e2.im, e3.re, e3.im};
+                    // direction by direction, as the products read them: two forward
+                    // entries of a mu and the two backward ones beside them
+                    nt_f4* dst = reinterpret_cast<nt_f4*>(lnk + sl * LSTR + j);
+                    dst[0] = nt_f4{e0.re, e0.im, e2.re, e2.im};
+                    dst[NCH] = nt_f4{e1.re, e1.im, e3.re, e3.im};
                 } else {
                     lnk[sl * LSTR + j] = v;
                 }
@@ -448,7 +451,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<S>& a, int bx, int d, int
                         const LE* le = reinterpret_cast<const LE*>(lnk + sl * LSTR);
 #pragma unroll
                         for (int k = 0; k < 9; ++k) {
-                            const LE t = le[link_slot<S>(DIR, k)];
+                            const LE t = le[DIR * 9 + k];
                             u[k] = {(T)t.x, (T)t.y};
                         }
                     } else if constexpr (S::has_scale) {

@@ -213,14 +213,15 @@ inline long hop_grid_x(long Vh, int Ls, int ndom, bool small, bool cg) {
 // matrix-core us (block: part of its widened box): in favour 24^4 in 12^4 (0.32) 780 /
 // 713, in 6x12x12x24 (0.34) 758 / 656, in two blocks (0.75) 514 / 434, 24^3x48 in 12^3x24
 // (0.36) 1372 / 1201, in 8^3x16 (0.24) 1622 / 1517, 16x24x28x32 in 4x12x14x16 (0.23) 919 /
-// 884; against 24^4 in 8^4 (0.20) 911 / 924, in 6^4 (0.13) 1086 / 1171, in 4^4 (0.06)
+// 884; against 48x16^3 in 12x8^3 (0.222) 521 / 522 (a step 664 / 688), 24^4 in 24x6^3
+// (0.216; a step 1118 / 1127), in 8^4 (0.20) 911 / 924, in 6^4 (0.13) 1086 / 1171, in 4^4 (0.06)
 // 1553 / 2149, and with fewer sites in the blocks 16^3x32 (65536) in 8^4 364 / 416,
 // 20^4 (80000) in 10^4 (0.26) 387 / 419.  A field's part of the largest box stays below
 // the reach of its 32-bit offsets.
 template <class S>
 inline bool hop_is_rows(long Vh, long inner, long widest, int Ls, int ndom) {
     return S::has_scale && Ls == 16 && Vh * ndom >= 150000 && inner * ndom >= 90000 &&
-           5 * inner >= widest && widest * Ls * 48 < 0x70000000;
+           9 * inner > 2 * widest && widest * Ls * 48 < 0x70000000;
 }
 // Whether a block hop visits its sites in the order of the traversal tile: the general
 // kernel onto a whole box

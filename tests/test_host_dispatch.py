@@ -90,6 +90,7 @@ def _boxes(dims, block, pad=2):
     ((16, 24, 28, 32), (4, 12, 14, 16), 2, 1), ((24, 24, 24, 24), (4, 4, 4, 4), 0, 1),
     # most of the widened blocks is rim
     ((24, 24, 24, 24), (8, 8, 8, 8), 2, 0), ((24, 24, 24, 24), (6, 6, 6, 6), 2, 0),
+    ((48, 16, 16, 16), (12, 8, 8, 8), 2, 0), ((24, 24, 24, 24), (24, 6, 6, 6), 2, 0),
     ((24, 24, 24, 48), (4, 4, 4, 4), 2, 0), ((16, 16, 16, 32), (4, 4, 4, 8), 2, 0),
     # too few sites in the blocks themselves
     ((20, 20, 20, 20), (10, 10, 10, 10), 2, 0), ((16, 16, 16, 32), (8, 8, 8, 8), 2, 0),
