@@ -45,10 +45,13 @@ __global__ __launch_bounds__(256) void fived_kernel(FiveDArgs<S> a) {
     if (active) {
         load_spinor_at<S>(a.in, ib, s, LS, v);
         if (a.xp_src.data) {
-            // what is read here is read before anything is stored: a load behind a
-            // store waits for a latency of its own (12^4x12 blocks in FP16 9.9 -> 9.3 us)
+            // AHEAD: src is read before z is stored, since a load behind a store waits for
+            // a latency of its own (12^4x12 blocks in FP16 9.9 -> 9.3 us), where its
+            // registers cost the CU no workgroup: in FP32 and FP16 at Ls <= 8 and 16, 73-80
+            // VGPRs against 84-92, they would (6 -> 5; 16^4x16 in FP16 28.3 -> 30.2 us)
+            constexpr bool AHEAD = sizeof(T) == 8 || (LS > 8 && LS != 16);
             cx<T> r[12];
-            load_spinor_at<S>(a.xp_src, ib, s, LS, r);
+            if constexpr (AHEAD) load_spinor_at<S>(a.xp_src, ib, s, LS, r);
             const T b = (T)(a.xp_beta ? a.xp_beta[d] : a.xp_sc->beta);
             if (a.zd_z.data) {
                 // deferred solution update z (+)= alpha p with the old p
@@ -68,6 +71,7 @@ __global__ __launch_bounds__(256) void fived_kernel(FiveDArgs<S> a) {
                 store_spinor_at<S>(a.zd_z, ib, s, LS, zv);
             }
             // search-direction update p = src + beta p, written back in place
+            if constexpr (!AHEAD) load_spinor_at<S>(a.xp_src, ib, s, LS, r);
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
                 v[c].re = r[c].re + b * v[c].re;

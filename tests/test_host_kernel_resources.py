@@ -1,5 +1,6 @@
 """Compiled kernels (no GPU): the registers that decide how many workgroups of the
-small-launch hop a CU holds; how the FP16 hop at Ls = 2 loads its links."""
+small-launch hop and of the 5D kernel a CU holds; how the FP16 hop at Ls = 2 loads its links."""
+import pathlib
 import re
 import subprocess
 
@@ -47,6 +48,29 @@ def test_small_hop_with_fused_update_keeps_its_residency(tmp_path, prec):
     for k in cases:
         room = 512 // (2 * WORKGROUPS[k]) // 8 * 8
         assert v[(*k, False)] <= room and v[(*k, True)] <= room, (k, v)
+
+
+def test_fived_kernel_keeps_its_residency(tmp_path):
+    """The 5D kernel's LDS lets a CU hold six workgroups of four waves in FP32 and FP16:
+    where the s-vector of a thread leaves them the room, its registers do too."""
+    build_dir = pathlib.Path(build.CSRC)
+    r = subprocess.run(["hipcc", *build.CXXFLAGS, "-I", build.CSRC, "--cuda-device-only", "-S",
+                        str(build_dir / "blas.hip"), "-o", str(tmp_path / "b.s")],
+                       capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    v, name = {}, None
+    for ln in (tmp_path / "b.s").read_text().splitlines():
+        m = re.match(r"\s*\.amdhsa_kernel \S*fived_kernelINS_3(F\d\d)ELi(\d+)E", ln)
+        if m:
+            name = (m[1], int(m[2]))
+        m = re.match(r"\s*\.amdhsa_next_free_vgpr (\d+)", ln)
+        if m and name:
+            v[name] = int(m[1])
+        if ".end_amdhsa_kernel" in ln:
+            name = None
+    for prec in ("F32", "F16"):
+        for ls in (2, 4, 6, 8, 16):
+            assert v[prec, ls] <= 512 // 6 // 8 * 8, (prec, ls, v)
 
 
 def test_fp16_hop_loads_unstaged_links_in_wide_loads(tmp_path):
