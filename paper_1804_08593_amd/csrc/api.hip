@@ -608,6 +608,14 @@ static int apply_prec(mspcg_ctx* c, int op, const double2* in, double2* out, hip
     if (op == MSPCG_OP_D || prepare) t[1] = half_field<S>(c, pfx + "ap_to", c->Nh);
     if ((full && !f[1].data) || (with_B && !t[0].data) || ((op == MSPCG_OP_D || prepare) && !t[1].data))
         return MSPCG_ENOMEM;
+    // the fields that the compositions below ask for themselves, so that a failure is
+    // MSPCG_ENOMEM and comes before anything is queued
+    auto there = [&](const char* name) { return half_field<S>(c, pfx + name, c->Nh).data != nullptr; };
+    const bool mhat = op == MSPCG_OP_MHAT || op == MSPCG_OP_A;
+    const bool mhatdag = op == MSPCG_OP_MHATDAG || op == MSPCG_OP_A || prepare;
+    if ((mhat && !there("mh_u")) || (mhatdag && !there("mh_v")) ||
+        (op == MSPCG_OP_A && !there("A_y")) || (prepare && !there("ap_te")))
+        return MSPCG_ENOMEM;
     const CField<S> fe = cfield(f[0]), fo = cfield(f[1]);
     T_(launch_pack_prog<S>(in, f, t, prepare ? P.X : P.B, c->act.mf, c->L, c->Ls, 0,
                            full || prepare ? 2 : 1, st));
