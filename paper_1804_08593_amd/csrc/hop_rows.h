@@ -29,14 +29,13 @@
 // whole wave and runs on the scalar unit; a dropped hop reads through a buffer
 // descriptor of length zero, which returns zeros without touching memory.
 //
-// 24^3 x 48 x 16 in 16 blocks, hops u / y / v of the block operator: 329 / 460 / 335 us
-// (general kernel 373 / 524 / 400).  v is bound by what passes between L2 and
-// memory, 6.1 TB/s; u by its vector instructions, issued two thirds of the time
-// (233 an output, 96 of them the scaled sums); y lies between.  More waves than 3
-// a SIMD need registers that spill (u 393 us at 4).  The hop with the fused
-// update stays with the general kernel: here it took 306 us, 489 with the update
-// of x (there 326 on average), and left the 5D kernel behind it less in cache (277
-// against 250 us).
+// 24^3 x 48 x 16 in 16 blocks, hops u / y / v of the block operator: 317 / 450 / 330 us
+// (general kernel 373 / 524 / 400).  v is bound by what passes between L2 and memory, 6.2
+// TB/s; u (3.4 TB/s) by its vector instructions, issued 71% of the time (233 an output,
+// 96 of them the scaled sums); y (4.8 TB/s, 65%) lies between.  More waves than 3 a SIMD
+// need registers that spill (u 393 us at 4).  The hop with the fused update stays with
+// the general kernel: here it took 306 us, 489 with the update of x (there 326 on
+// average), and left the 5D kernel behind it less in cache (277 against 250 us).
 // The 5D programs move values along s with DPP row shifts instead of LDS.
 //
 #pragma once
