@@ -30,8 +30,8 @@
 #endif
 // MSPCG_HOP_PF{64,32,16}: directions whose raw neighbour spinors are loaded
 // before any of them is decoded and applied (per storage precision).  Two
-// for FP16 (12^3x24 domain hop at Ls = 16 428 -> 415 us); deeper groups did not help the FP64 and FP32
-// hops.
+// for FP16 (12^3x24 domain hop at Ls = 16 428 -> 415 us); deeper groups did not
+// help the FP64 and FP32 hops.
 #ifndef MSPCG_HOP_PF64
 #define MSPCG_HOP_PF64 1
 #endif
@@ -248,7 +248,7 @@ __device__ __forceinline__ void sfor(F&& f) {
 // staged in LDS with coalesced 16-byte loads (one load per 16 bytes of links
 // instead of one per element and lane) when they fit; the epilogue reuses
 // that LDS after the direction loop.
-// FP16-storage hops at Ls = 8 or 16 without an aux chain or fused CG update
+// FP16-storage hops at Ls = 8 without an aux chain or fused CG update
 // fit in 80 VGPRs without spilling: ask for 6 waves per SIMD there (their
 // arithmetic, not memory, sets the pace)
 template <class S, int LS, bool EPA, bool CG>
